@@ -132,11 +132,9 @@ SCALAR_ISSUE_PEAK = 256 * 2.4
 
 def kernel_name(lim):
     """Which replay kernel the library picks for these batch limits (the compact one when every
-    limit fits its 16-bit encoding: up to 64 live claims on up to 256 chains, or up to 256 live
-    claims on up to 64 chains)."""
-    claims_ok = (lim["max_live_claims"] <= 64 and lim["max_chains"] <= 256) or \
-                (lim["max_live_claims"] <= 256 and lim["max_chains"] <= 64)
-    fits = (lim["max_usable_blocks"] <= 32767 and lim["max_events"] <= 65533 and claims_ok
+    limit fits its 16-bit encoding)."""
+    fits = (lim["max_usable_blocks"] <= 32767 and lim["max_events"] <= 65533
+            and lim["max_live_claims"] <= 256 and lim["max_chains"] <= 256
             and lim["max_live_requests"] <= 256 and lim["max_claim_slots"] <= 65534)
     return "rkc_lean" if fits else "rkc_replay_wave"
 

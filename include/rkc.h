@@ -293,7 +293,7 @@ typedef struct rkc_batch {
 
 /* rkc_batch.flags: replay with the general kernel even when the batch fits the compact one (the
  * compact kernel is chosen for usable blocks <= 32,767, events <= 65,533, chains <= 256, live
- * claims <= 64 and live requests <= 256).  Both give identical outputs; the flag exists so the
+ * claims <= 256 and live requests <= 256).  Both give identical outputs; the flag exists so the
  * general kernel can be checked on the same inputs. */
 #define RKC_FLAG_GENERAL_KERNEL 1
 /* rkc_batch.flags: one wavefront per pool everywhere.  Without it, a batch of at most 256 pools (one

@@ -27,8 +27,7 @@ struct rkc_lean_args {
 };
 
 // Fill the layout part of g for batch b; false when b is outside the compact kernel's limits
-// (usable blocks <= 32,767, events <= 65,533, live requests <= 256, and live claims <= 64 with
-// chains <= 256 or live claims <= 256 with chains <= 64).
+// (usable blocks <= 32,767, events <= 65,533, live requests, live claims and chains <= 256).
 bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g);
 
 // Launch the compact kernel (one 64-lane workgroup per pool) on stream s.

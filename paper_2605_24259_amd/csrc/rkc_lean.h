@@ -18,6 +18,7 @@ struct rkc_lean_args {
   int64_t n_events_total, n_slots_total;
   int32_t n_pools, max_usable, max_events, max_chains, max_reqs, max_claims, max_slots;
   // layout: LDS byte offsets, node split, per-pool scratch regions
+  uint32_t ordered;  // the launch groups the pools by event loop
   uint32_t ns, nq, node_cap, nodes_lds;  // 64-chain key groups, 64-claim sets, node split
   uint32_t lds_bytes;  // LDS per pool (its regions sit at offsets fixed per kernel instantiation)
   uint64_t scr_pool_bytes, scr_off_nodes, scr_off_fifo, scr_off_slots, scr_off_defer, scr_off_reqs;

@@ -1483,12 +1483,19 @@ __device__ __forceinline__ u32 loop_class(const rkc_pool_desc& d) {
 }
 
 // Launch order: the pools grouped by the event loop they run, so that the workgroups resident on a
-// CU execute one loop and share its instructions in the instruction cache (pools of mixed policies
-// side by side thrash it: ~9 % of the replay time on a batch cycling through the four policies).
+// CU execute one loop and share its instructions in the instruction cache, and every CU gets its
+// share of the heavy loops (pools of mixed policies side by side thrash the cache and, dealt out
+// with a period that divides the CU count, load the CUs unevenly: 6,400 pools cycling through the
+// four policies take 1.86 ms in batch order, 1.47 ms grouped).  Every pool index appears exactly once
+// and the replay does not depend on the order: pools are grouped by class, within a class in
+// wave-arrival order per tile.  Batches that stay in batch order are those of short traces, whose
+// replay is not longer than the passes, and those of at most one pool per SIMD, where each loop
+// has its SIMD to itself (1,024 pools of 80 blocks x 256 events: 184 us in batch order, 191 us
+// grouped; 2,048 pools of 2,048 blocks x 1,024 events: 972 us in batch order, 930 us grouped).
 // Two short passes over 1,024-pool tiles: count each tile's pools per loop class, then scatter
-// every pool to its class's range (tiles in order, pools within a tile in wave-arrival order).
-// Every pool index appears exactly once; the replay does not depend on the order.
-constexpr u32 kOrderTile = 1024, kClasses = 6;
+// every pool to its class's range.  (One workgroup ordering up to 8 tiles in a single launch was no
+// faster: 4,096 pools of 80 blocks x 256 events 221 us against 218 us.)
+constexpr u32 kOrderTile = 1024, kClasses = 6, kOrderMinPools = 1024, kOrderMinEvents = 64;
 
 __global__ __launch_bounds__(1024) void rkc_lean_order_count(const rkc_pool_desc* pools, i32 n_pools,
                                                               unsigned char* cls, u32* tile_count) {
@@ -1537,14 +1544,8 @@ __global__ __launch_bounds__(1024) void rkc_lean_order_scatter(i32 n_pools, cons
   }
 }
 
-// Batch order (pools of a few events: grouping them by event loop does not pay for its passes).
-__global__ __launch_bounds__(1024) void rkc_lean_order_identity(i32 n_pools, u32* order) {
-  const i32 p = (i32)(blockIdx.x * kOrderTile + threadIdx.x);
-  if (p < n_pools) order[p] = (u32)p;
-}
-
-// One wavefront per pool, in the launch order above; the pool's policy selects its specialized
-// event loop once.  With four claim sets the registers, not LDS, bound residency: the kernel is
+// One wavefront per pool, in the launch order above (or batch order); the pool's policy selects its
+// specialized event loop once.  With four claim sets the registers, not LDS, bound residency: the kernel is
 // held to 6 waves per SIMD (80 vector registers, a few values spilled to scratch; 5 waves and 93
 // registers otherwise, measured slower: nested 9.9 vs 9.3 ms).
 template <int NS, int NQ>
@@ -1553,7 +1554,7 @@ template <int NS, int NQ>
 __global__ __launch_bounds__(64, NQ > 1 ? 6 : 1) void rkc_lean(rkc_lean_args g, const rkc_event* __restrict__ evs) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   if ((i32)blockIdx.x >= g.n_pools) return;
-  const u32 pool = ((const u32*)((const unsigned char*)g.scratch + g.scr_off_order))[blockIdx.x];
+  const u32 pool = g.ordered ? ((const u32*)((const unsigned char*)g.scratch + g.scr_off_order))[blockIdx.x] : blockIdx.x;
   const u32 lane = __lane_id();
   const rkc_pool_desc d = g.pools[pool];
   const i64 ev_off = d.event_offset, slot_off = d.claim_slot_offset;
@@ -1630,11 +1631,12 @@ bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g) {
   g->scr_off_reqs = s; s += 8ull * (reqs > rql ? reqs - rql : 0u);
   g->scr_pool_bytes = align_up(s, 256);
   const u64 np = b->n_pools > 0 ? (u64)b->n_pools : 0u;
+  g->ordered = (u32)b->max_events >= kOrderMinEvents && np > kOrderMinPools;
   const u64 tiles = (np + kOrderTile - 1) / kOrderTile;
   g->scr_off_order = g->scr_pool_bytes * np;
   g->scr_off_cls = g->scr_off_order + align_up(4ull * np, 256);
   g->scr_off_tiles = g->scr_off_cls + align_up(np, 256);
-  g->scr_total = g->scr_off_tiles + align_up(4ull * kClasses * tiles, 256);
+  g->scr_total = g->ordered ? g->scr_off_tiles + align_up(4ull * kClasses * tiles, 256) : g->scr_off_order;
   return true;
 }
 
@@ -1653,19 +1655,15 @@ rkc_status launch_ns(const rkc_lean_args* g, hipStream_t s) {
                           (int)g->lds_bytes) != hipSuccess)
     return RKC_E_HIP;
   unsigned char* scr = (unsigned char*)g->scratch;
-  const unsigned tiles = (unsigned)(((u64)g->n_pools + kOrderTile - 1) / kOrderTile);
-  if (g->max_events >= 64) {
-    // long event loops: group the pools by loop so that a CU's resident pools share one loop
+  if (g->ordered) {
+    const unsigned tiles = (unsigned)(((u64)g->n_pools + kOrderTile - 1) / kOrderTile);
+    u32* order = (u32*)(scr + g->scr_off_order);
     hipLaunchKernelGGL(rkc_lean_order_count, dim3(tiles), dim3(kOrderTile), 0, s, g->pools, (i32)g->n_pools,
                        scr + g->scr_off_cls, (u32*)(scr + g->scr_off_tiles));
     hipLaunchKernelGGL(rkc_lean_order_scatter, dim3(tiles), dim3(kOrderTile), 0, s, (i32)g->n_pools,
-                       (const unsigned char*)(scr + g->scr_off_cls), (const u32*)(scr + g->scr_off_tiles),
-                       (u32*)(scr + g->scr_off_order));
-  } else {
-    hipLaunchKernelGGL(rkc_lean_order_identity, dim3(tiles), dim3(kOrderTile), 0, s, (i32)g->n_pools,
-                       (u32*)(scr + g->scr_off_order));
+                       (const unsigned char*)(scr + g->scr_off_cls), (const u32*)(scr + g->scr_off_tiles), order);
+    if (hipGetLastError() != hipSuccess) return RKC_E_HIP;
   }
-  if (hipGetLastError() != hipSuccess) return RKC_E_HIP;
   hipLaunchKernelGGL((rkc_lean<NS, NQ>), dim3((unsigned)g->n_pools), dim3(64), g->lds_bytes, s, *g, g->events);
   return hipGetLastError() == hipSuccess ? RKC_OK : RKC_E_HIP;
 }

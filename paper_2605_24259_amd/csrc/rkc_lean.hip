@@ -1631,12 +1631,17 @@ bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g) {
   g->scr_off_reqs = s; s += 8ull * (reqs > rql ? reqs - rql : 0u);
   g->scr_pool_bytes = align_up(s, 256);
   const u64 np = b->n_pools > 0 ? (u64)b->n_pools : 0u;
-  g->ordered = (u32)b->max_events >= kOrderMinEvents && np > kOrderMinPools;
+  // (many claims over many chains: from 128 events on the scratch with the order is smaller than the
+  // general kernel's, and below the unused order takes none, so no batch that fitted the built-in
+  // scratch on the general kernel is refused here)
+  const bool many = g->nq == 4 && ns > 1;
+  g->ordered = (u32)b->max_events >= (many ? 2 * kOrderMinEvents : kOrderMinEvents) && np > kOrderMinPools;
   const u64 tiles = (np + kOrderTile - 1) / kOrderTile;
   g->scr_off_order = g->scr_pool_bytes * np;
   g->scr_off_cls = g->scr_off_order + align_up(4ull * np, 256);
   g->scr_off_tiles = g->scr_off_cls + align_up(np, 256);
-  g->scr_total = g->ordered ? g->scr_off_tiles + align_up(4ull * kClasses * tiles, 256) : g->scr_off_order;
+  g->scr_total = g->scr_off_tiles + align_up(4ull * kClasses * tiles, 256);
+  if (many && !g->ordered) g->scr_total = g->scr_off_order;
   return true;
 }
 

@@ -130,17 +130,21 @@ def profile_record(kernel, workload, kernel_sha):
 SCALAR_ISSUE_PEAK = 256 * 2.4
 
 
-def kernel_name(lim):
+def kernel_name(lim, n_pools=0):
     """Which replay kernel the library picks for these batch limits (the compact one when every
-    limit fits its 16-bit encoding)."""
+    limit fits its 16-bit encoding, one lane per pool when the traces are very short)."""
     fits = (lim["max_usable_blocks"] <= 32767 and lim["max_events"] <= 65533
             and lim["max_live_claims"] <= 256 and lim["max_chains"] <= 256
             and lim["max_live_requests"] <= 256 and lim["max_claim_slots"] <= 65534)
+    if fits and lim["max_claim_slots"] <= 8 and lim["max_events"] <= (4 if n_pools >= 49152 else 2):
+        return "rkc_tiny"
     return "rkc_lean" if fits else "rkc_replay_wave"
 
 
 def parallelism(trace, kernel):
     """How pools map to the GPU for this batch (mirrors the library's launch choice)."""
+    if kernel == "rkc_tiny":
+        return "one lane per pool"
     if kernel == "rkc_lean":
         return "one wavefront per pool"
     lim = trace.limits()
@@ -153,6 +157,8 @@ def parallelism(trace, kernel):
 
 
 KERNEL_SOURCES = {
+    "rkc_tiny": ("paper_2605_24259_amd/csrc/rkc_tiny.hip", "paper_2605_24259_amd/csrc/rkc_tiny.h",
+                 "include/rkc.h", "paper_2605_24259_amd/build.py"),
     "rkc_lean": ("paper_2605_24259_amd/csrc/rkc_lean.hip", "paper_2605_24259_amd/csrc/rkc_lean.h",
                  "include/rkc.h", "paper_2605_24259_amd/build.py"),
     "rkc_replay_wave": ("paper_2605_24259_amd/csrc/rkc_replay.hip", "include/rkc.h",
@@ -243,7 +249,8 @@ def main():
     ceiling = copy_ceiling(torch)
     base = None if args.no_cpu_baseline else cpu_baseline(trace)
     lim = trace.limits()
-    prof = profile_record(kernel_name(lim), args.workload, kernel_source_sha(kernel_name(lim)))
+    kernel = kernel_name(lim, trace.n_pools)
+    prof = profile_record(kernel, args.workload, kernel_source_sha(kernel))
     salu = prof.get("sq_insts_salu_per_launch")
     line = {
         "metric": METRIC,
@@ -263,8 +270,8 @@ def main():
                         f"blocks x {lim['max_events']} events",
             "pools": trace.n_pools, "usable_blocks": lim["max_usable_blocks"],
             "events_per_pool": lim["max_events"], "events_per_step": events,
-            "claim_slots": trace.n_claim_slots, "parallelism": parallelism(trace, kernel_name(lim)),
-            "kernel": kernel_name(lim),
+            "claim_slots": trace.n_claim_slots, "parallelism": parallelism(trace, kernel),
+            "kernel": kernel,
         },
         "roofline": {
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",

@@ -293,7 +293,8 @@ typedef struct rkc_batch {
 
 /* rkc_batch.flags: replay with the general kernel even when the batch fits the compact one (the
  * compact kernel is chosen for usable blocks <= 32,767, events <= 65,533, chains <= 256, live
- * claims <= 256 and live requests <= 256).  Both give identical outputs; the flag exists so the
+ * claims <= 256 and live requests <= 256; of those, batches of at most two events a pool, or four when
+ * they are large, are replayed by one lane per pool).  All give identical outputs; the flag exists so the
  * general kernel can be checked on the same inputs. */
 #define RKC_FLAG_GENERAL_KERNEL 1
 /* rkc_batch.flags: one wavefront per pool everywhere.  Without it, a batch of at most 256 pools (one
@@ -322,8 +323,8 @@ int32_t rkc_abi_version(void);
  * defines no storage, only the contract the replay follows): per pool, the pool state that does not
  * stay on chip (touch-stack nodes beyond the LDS part, the FIFO of finished requests' private runs,
  * one entry per claim slot, a deferral ring of max_live_requests entries, and the live lists when
- * they do not fit in LDS), plus some bytes per pool for the compact kernel's launch order (large
- * batches of long traces).  Reads only the host-side limits of b; never fails (returns 0 for a NULL b or an empty batch). */
+ * they do not fit in LDS), plus some bytes per pool for the compact kernel's launch order.
+ * Reads only the host-side limits of b; never fails (returns 0 for a NULL b or an empty batch). */
 size_t rkc_scratch_bytes(const rkc_batch* b);
 
 /* Replay every pool of the batch from empty pools (all U blocks FREE, no claims, no requests).

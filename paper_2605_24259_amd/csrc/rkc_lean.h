@@ -34,6 +34,10 @@ bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g);
 // Launch the compact kernel (one 64-lane workgroup per pool) on stream s.
 rkc_status rkc_lean_launch(const rkc_lean_args* g, hipStream_t s);
 
+// Batches of short traces: a lane replays a pool (rkc_tiny.hip).
+bool rkc_tiny_fits(const rkc_lean_args* g);
+rkc_status rkc_tiny_launch(const rkc_lean_args* g, hipStream_t s);
+
 #ifdef RKC_CHECK_UNIFORM
 // checking build only: calls of the compact kernel's readfirstlane whose active lanes disagreed
 unsigned rkc_lean_uniform_violations(void);

@@ -1809,7 +1809,7 @@ static rkc_status replay(const rkc_batch* b, void* s) {
     lg.n_pools = b->n_pools; lg.max_usable = b->max_usable_blocks; lg.max_events = b->max_events;
     lg.max_chains = b->max_chains; lg.max_reqs = b->max_live_requests; lg.max_claims = b->max_live_claims;
     lg.max_slots = b->max_claim_slots;
-    return rkc_lean_launch(&lg, (hipStream_t)s);
+    return rkc_tiny_fits(&lg) ? rkc_tiny_launch(&lg, (hipStream_t)s) : rkc_lean_launch(&lg, (hipStream_t)s);
   }
   Args g;
   memset(&g, 0, sizeof g);

@@ -132,20 +132,23 @@ SCALAR_ISSUE_PEAK = 256 * 2.4
 
 def kernel_name(lim, n_pools=0):
     """Which replay kernel the library picks for these batch limits (the compact one when every
-    limit fits its 16-bit encoding, one lane per pool when the traces are very short)."""
+    limit fits its 16-bit encoding, one lane per pool when the traces are very short, the
+    large-pool one within its limits)."""
     fits = (lim["max_usable_blocks"] <= 32767 and lim["max_events"] <= 65533
             and lim["max_live_claims"] <= 256 and lim["max_chains"] <= 256
             and lim["max_live_requests"] <= 256 and lim["max_claim_slots"] <= 65534)
     if fits and lim["max_claim_slots"] <= 8 and lim["max_events"] <= (4 if n_pools >= 49152 else 2):
         return "rkc_tiny"
-    return "rkc_lean" if fits else "rkc_replay_wave"
+    big = (lim["max_usable_blocks"] < 1 << 20 and lim["max_events"] <= 65536 and lim["max_chains"] <= 256
+           and lim["max_live_requests"] <= 16384 and lim["max_claim_slots"] <= 65536)
+    return "rkc_lean" if fits else "rkc_big" if big else "rkc_replay_wave"
 
 
 def parallelism(trace, kernel):
     """How pools map to the GPU for this batch (mirrors the library's launch choice)."""
     if kernel == "rkc_tiny":
         return "one lane per pool"
-    if kernel == "rkc_lean":
+    if kernel in ("rkc_lean", "rkc_big"):
         return "one wavefront per pool"
     lim = trace.limits()
     # the general kernel keeps the live lists in LDS when they fit beside the chain records
@@ -161,6 +164,8 @@ KERNEL_SOURCES = {
                  "include/rkc.h", "paper_2605_24259_amd/build.py"),
     "rkc_lean": ("paper_2605_24259_amd/csrc/rkc_lean.hip", "paper_2605_24259_amd/csrc/rkc_lean.h",
                  "include/rkc.h", "paper_2605_24259_amd/build.py"),
+    "rkc_big": ("paper_2605_24259_amd/csrc/rkc_big.hip", "paper_2605_24259_amd/csrc/rkc_big.h",
+                "include/rkc.h", "paper_2605_24259_amd/build.py"),
     "rkc_replay_wave": ("paper_2605_24259_amd/csrc/rkc_replay.hip", "include/rkc.h",
                         "paper_2605_24259_amd/build.py"),
 }

@@ -294,12 +294,13 @@ typedef struct rkc_batch {
 /* rkc_batch.flags: replay with the general kernel even when the batch fits the compact one (the
  * compact kernel is chosen for usable blocks <= 32,767, events <= 65,533, chains <= 256, live
  * claims <= 256 and live requests <= 256; of those, batches of at most two events a pool, or four when
- * they are large, are replayed by one lane per pool).  All give identical outputs; the flag exists so the
- * general kernel can be checked on the same inputs. */
+ * they are large, are replayed by one lane per pool) or the large-pool one (usable blocks < 2^20,
+ * events <= 65,536, chains <= 256, live requests <= 16,384).  All give identical outputs; the flag
+ * exists so the general kernel can be checked on the same inputs. */
 #define RKC_FLAG_GENERAL_KERNEL 1
 /* rkc_batch.flags: one wavefront per pool everywhere.  Without it, a batch of at most 256 pools (one
- * per compute unit) whose live lists do not fit in LDS is replayed by a workgroup of 8 wavefronts
- * per pool (wave 0 runs the pool's event loop; the others share the scans and moves of its long
+ * per compute unit) that the general kernel serves and whose live lists do not fit in LDS is replayed
+ * by a workgroup of 8 wavefronts per pool (wave 0 runs the pool's event loop; the others share the scans and moves of its long
  * lists).  Both give identical outputs; the flag exists so both can be checked on the same inputs. */
 #define RKC_FLAG_ONE_WAVE_PER_POOL 2
 

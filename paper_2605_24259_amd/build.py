@@ -6,7 +6,8 @@ import subprocess
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SRCS = [os.path.join(PKG, "csrc", f) for f in ("rkc_replay.hip", "rkc_lean.hip", "rkc_tiny.hip")]
+SRCS = [os.path.join(PKG, "csrc", f) for f in ("rkc_replay.hip", "rkc_lean.hip", "rkc_big.hip",
+                                              "rkc_tiny.hip")]
 LIB = os.path.join(PKG, "librkc.so")
 ARCH = "gfx950"
 

@@ -42,6 +42,7 @@
 #include <mutex>
 
 #include "rkc.h"
+#include "rkc_big.h"
 #include "rkc_lean.h"
 
 // Built-in device scratch of rkc_replay_batch_noalloc, for callers that cannot allocate.  Each device
@@ -1780,6 +1781,16 @@ bool use_lean(const rkc_batch* b, rkc_lean_args* g) {
   return !(b->flags & RKC_FLAG_GENERAL_KERNEL) && rkc_lean_layout(b, g);
 }
 
+// The large-pool kernel serves the other batches within its limits unless the caller asks for the
+// general one.  (A batch that would need more scratch there than on the general kernel, where long
+// claim lists may fit in LDS, stays on the general one: the scratch a batch needs never grows.)
+bool use_big(const rkc_batch* b, rkc_big_args* g) {
+  memset(g, 0, sizeof *g);
+  Layout L;
+  return !(b->flags & RKC_FLAG_GENERAL_KERNEL) && rkc_big_layout(b, g) &&
+         choose_layout(b, &L) && g->scr_pool_bytes <= L.scr_pool_bytes;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1790,6 +1801,8 @@ size_t rkc_scratch_bytes(const rkc_batch* b) {
   if (!b || b->n_pools <= 0) return 0;
   rkc_lean_args lg;
   if (use_lean(b, &lg)) return (size_t)lg.scr_total;
+  rkc_big_args bg;
+  if (use_big(b, &bg)) return (size_t)(bg.scr_pool_bytes * (u64)b->n_pools);
   Layout L;
   if (!choose_layout(b, &L)) return 0;
   return (size_t)(L.scr_pool_bytes * (u64)b->n_pools);
@@ -1810,6 +1823,17 @@ static rkc_status replay(const rkc_batch* b, void* s) {
     lg.max_chains = b->max_chains; lg.max_reqs = b->max_live_requests; lg.max_claims = b->max_live_claims;
     lg.max_slots = b->max_claim_slots;
     return rkc_tiny_fits(&lg) ? rkc_tiny_launch(&lg, (hipStream_t)s) : rkc_lean_launch(&lg, (hipStream_t)s);
+  }
+  rkc_big_args bg;
+  if (use_big(b, &bg)) {
+    if (!b->d_scratch || b->scratch_bytes < bg.scr_pool_bytes * (u64)b->n_pools) return RKC_E_SCRATCH;
+    bg.pools = b->d_pools; bg.events = b->d_events; bg.outcomes = b->d_outcomes;
+    bg.pool_tel = b->d_pool_tel; bg.claim_tel = b->d_claim_tel; bg.scratch = b->d_scratch;
+    bg.n_events_total = b->n_events_total; bg.n_slots_total = b->n_claim_slots_total;
+    bg.n_pools = b->n_pools; bg.max_usable = b->max_usable_blocks; bg.max_events = b->max_events;
+    bg.max_chains = b->max_chains; bg.max_reqs = b->max_live_requests; bg.max_claims = b->max_live_claims;
+    bg.max_slots = b->max_claim_slots;
+    return rkc_big_launch(&bg, (hipStream_t)s);
   }
   Args g;
   memset(&g, 0, sizeof g);
@@ -1924,7 +1948,8 @@ uint32_t rkc_debug_uniform_violations(void) {
   unsigned v = 0;
   if (hipMemcpyFromSymbol(&v, HIP_SYMBOL(g_wave_uniform_violations), sizeof v) != hipSuccess) return ~0u;
   const unsigned w = rkc_lean_uniform_violations();
-  return w == ~0u ? ~0u : v + w;
+  const unsigned x = rkc_big_uniform_violations();
+  return w == ~0u || x == ~0u ? ~0u : v + w + x;
 }
 #endif
 

@@ -48,3 +48,83 @@ def test_four_event_pools(oracle_mod, tg, n_pools):
     assert (out[: whole * base.n_events].reshape(whole, -1, 4) == o_out).all()
     assert (pt[: whole * base.n_pools].reshape(whole, -1, 64) == o_pt).all()
     assert (ct[: whole * base.n_claim_slots].reshape(whole, -1, 10) == o_ct).all()
+
+
+def _big(trace, **limits):
+    """The trace with batch limits past the compact kernel's (the large-pool kernel replays it)."""
+    import paper_2605_24259_amd as rkc
+    lim = dict(trace.limits(), **limits)
+    lim["max_usable_blocks"] = max(lim["max_usable_blocks"], 40000)
+    return rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, lim).replay().results()
+
+
+# the large-pool kernel: every feature, table overflows, more pools than CUs and fewer
+@pytest.mark.parametrize("n_pools", [40, 700])
+@pytest.mark.parametrize("kw", [dict(), dict(defer=True, hard_share=0.7), dict(relax=True, offload=True, hard_share=0.8),
+                                dict(defer=True, relax=True, offload=True, hard_share=0.8)],
+                         ids=["plain", "defer", "offload", "all"])
+def test_large_pool_kernel_random(oracle_mod, n_pools, kw):
+    trace = randtrace.random_batch(300 + n_pools, n_pools, U_range=(4, 300), n_events=(1, 400), n_chains=9,
+                                   p_malformed=0.01, tight_every=5, **kw)
+    say(f"case large-pool random {n_pools} {kw}")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    compare_pools(trace, _big(trace), ora)
+
+
+# its request ring: tables of 1 to 6 entries, whose ring wraps all the time, and at its largest
+@pytest.mark.parametrize("max_live_requests", [6, 16384])
+def test_large_pool_kernel_request_ring(oracle_mod, max_live_requests):
+    trace = randtrace.many_requests_batch(17, 48, n_events=(900, 1500), n_chains=200, req_cap=1024)
+    if max_live_requests < 1024:
+        trace.desc[:, 5] = np.minimum(trace.desc[:, 5], max_live_requests)
+    say(f"case request ring {max_live_requests}")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    compare_pools(trace, _big(trace, max_live_requests=max_live_requests), ora)
+
+
+# its claim list past the 256 claims kept in LDS, and long lists of both kinds
+@pytest.mark.parametrize("claim_cap", [256, 257, 900])
+def test_large_pool_kernel_claim_list(oracle_mod, claim_cap):
+    trace = randtrace.many_claims_batch(55, 64, n_events=(900, 2500), claim_cap=claim_cap, n_chains=80,
+                                        claim_share=0.6, release_share=0.06)
+    say(f"case claim list {claim_cap}")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    assert claim_cap < 900 or ora[1][:, 30].max() > 320
+    compare_pools(trace, _big(trace, max_live_requests=4096), ora)
+
+
+def test_large_pool_kernel_long_lists(oracle_mod, tg):
+    from tests.test_gpu_group import long_list_pools
+    trace = long_list_pools(tg, 103, 8)
+    say("case large-pool long lists")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    compare_pools(trace, gpu_replay(trace), ora)
+
+
+# the edges of its encoding: 2^20 - 1 blocks and 65,536 events go there, one more of either does not
+@pytest.mark.parametrize("usable,events", [((1 << 20) - 1, 65536), (1 << 20, 65536), ((1 << 20) - 1, 65537)])
+def test_large_pool_kernel_limits(tg, usable, events):
+    import paper_2605_24259_amd as rkc
+    sel = [(i * 2654435761) & 0x7FFFFFFF for i in range(events)]
+    evs = []
+    for i in range(events):
+        k = i % 16
+        if i == events - 1:
+            evs.append(tg.prefill(usable // 2, 255, usable // 2))
+        elif k in (0, 5, 10):
+            evs.append(tg.prefill(1 + sel[i] % (usable // 3), sel[i] % 256, (1 + sel[i] % (usable // 3)) // 2))
+        elif k in (3, 8):
+            evs.append(tg.claim(1 + sel[i] % (usable // 5), sel[i] % 256, hard=i & 1, prio=i & 3, dur=sel[i] % 65536))
+        elif k == 12:
+            evs.append(tg.release(sel[i]))
+        elif k in (4, 14):
+            evs.append(tg.finish(sel[i]))
+        else:
+            evs.append(tg.extend(1 + sel[i] % 50, sel[i]))
+    trace = tg.from_pools([dict(usable_blocks=usable, mode=m, n_chains=256, max_live_requests=9000, max_live_claims=300,
+                                events=evs) for m in range(4)])
+    say(f"case large-pool limits {usable} {events}")
+    got = gpu_replay(trace)
+    gen = gpu_replay(trace, flags=rkc.FLAG_GENERAL_KERNEL)
+    assert not (got[1][:, 31] & ~7).any()
+    compare_pools(trace, got, gen)

@@ -14,11 +14,16 @@
 //     top, stack bottom) is read once per event into scalar registers; every branch is wave-uniform;
 //   - the pool policy selects an event loop specialized at compile time;
 //   - claims are 16 bytes (id | chain, L, T, meta | duration) plus slot and blocked count, the first
-//     256 in LDS; their steps go straight into their telemetry records;
+//     64 in registers, one per lane, the next 192 in LDS; their steps go straight into their
+//     telemetry records;
 //   - touch-stack nodes take the LDS the rest leaves, then global scratch.
 // Representation, eviction order and why they are exact: rkc_lean.hip.
-// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 135.3 -> 66.8 ms,
-// 512 pools of 65,536 blocks x 4,096 events 7.66 -> 4.19 ms (about 1 us an event either way).
+// A step is a chain of LDS round trips (~130 cycles each), so the first 64 claims and the FIFO's
+// front sit in registers, loads are issued before they are needed (free-list head, FIFO's next run,
+// hold count), and touching the prefix that was touched last only rewrites a step (4.17 -> 3.52 ms
+// and 60.9 -> 54.5 ms on the batches below).
+// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 135.3 -> 54.5 ms,
+// 512 pools of 65,536 blocks x 4,096 events 7.66 -> 3.52 ms (under 1 us an event either way).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -121,6 +126,10 @@ __device__ __forceinline__ u32 wreduce(u32 v) {
 __device__ __forceinline__ u32 wmax(u32 v) { return wreduce<OpMax>(v); }
 __device__ __forceinline__ u32 wmin(u32 v) { return wreduce<OpMin>(v); }
 __device__ __forceinline__ u32 wsum(u32 v) { return wreduce<OpAdd>(v); }
+// lane l receives lane l + 1's value (lane 63 keeps its own)
+__device__ __forceinline__ u32 shift_down(u32 v) {
+  return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
+}
 
 // chain record (two 16-byte groups)
 struct G0 { u32 n, hold, prot, bt, nx, covA, stop, sbot; };
@@ -165,8 +174,8 @@ struct Big {
   lds_u32* hcnt;     // live requests holding exactly the chain's hold
   lds_u32* mark;     // 256 chain bits: chains to recompute
   lds_u32x4* ch;
-  lds_u32x4* cll;    // claims [0, 256): id | chain << 16, L, T, meta | duration << 16
-  lds_u32x2* cxl;    // slot, blocked count
+  lds_u32x4* cll;    // claims [64, 256)
+  lds_u32x2* cxl;
   glb_u32x4* clg;    // claims past them
   glb_u32x2* cxg;
   lds_u32x2* rq;     // ring
@@ -174,7 +183,7 @@ struct Big {
   lds_u32x4* ndl;    // nodes: extent, step, up (newer), down (older)
   glb_u32x4* ndg;
   u32 nl;
-  glb_u32x4* fifo;   // finished requests' private runs: finish step, low end, top
+  glb_u32x2* fifo;   // finished requests' private runs: low end:20 step_lo:12 | top:20 step_hi:4
   glb_u32x2* slot2;  // per slot: L | chain << 20, and NEVER or a rejected claim's id | packed word
   glb_u32x4* dq;     // deferred requests: PREFILL step, S, chain, P
   rkc_claim_telemetry* rec;
@@ -185,9 +194,36 @@ struct Big {
   u32 tv;  // pool telemetry word `lane`
   u32 F, A, PR, peak, E;
   u32 nreq, ncl, nexp, sweep_due, vic, post, nslot;
-  u32 fkey;  // eviction key of the front private run, KINF when there is none
+  // FIFO of private runs: head, tail, the front run's eviction key (KINF when there is none) and
+  // bounds, and the run behind it (loaded ahead, so that taking a whole run does not wait for memory)
+  u32 qh, qt, fkey, flo, ftop;
+  u32x2 fnext;
+  __device__ __forceinline__ static u32x2 run_pack(u32 t, u32 lo, u32 top) { return u32x2{lo | (t << 20), top | ((t >> 12) << 20)}; }
+  __device__ __forceinline__ void fifo_pop() {
+    qh++;
+    fkey = KINF;
+    if (qh != qt) {
+      const u32 a = ufl(fnext.x), b = ufl(fnext.y);
+      fkey = ((a >> 20) | ((b >> 20) << 12)) << 9;
+      flo = a & 0xFFFFFu;
+      ftop = b & 0xFFFFFu;
+      if (qh + 1 != qt) fnext = fifo[qh + 1];
+    }
+  }
+  __device__ __forceinline__ void fifo_push(u32 t, u32 lo, u32 top) {
+    const u32x2 e = run_pack(t, lo, top);
+    if (qh == qt) {
+      fkey = t << 9;
+      flo = lo;
+      ftop = top;
+    } else if (qh + 1 == qt) {
+      fnext = e;
+    }
+    fifo[qt] = e;  // every lane, one value
+    qt++;
+  }
   // scalars that only a few paths touch
-  enum : u32 { C_QH = 0, C_QT, C_FLO, C_FTOP, C_FNODE, C_BUMP, C_STATUS, C_T2, C_DQH, C_DQL, C_DQC, C_T2PK, C_WORDS };
+  enum : u32 { C_STATUS = 0, C_T2, C_DQH, C_DQL, C_DQC, C_T2PK, C_WORDS };
   __device__ __forceinline__ u32 cget(u32 w) const { return ufl(cold[w]); }
   __device__ __forceinline__ void set_status(u32 bits) { cold[C_STATUS] = cget(C_STATUS) | bits; }
 
@@ -303,62 +339,96 @@ struct Big {
     if (i < nl) ((lds_u32x2*)(ndl + i))[1] = u32x2{up, down};
     else ((glb_u32x2*)(ndg + (i - nl)))[1] = u32x2{up, down};
   }
+  __device__ __forceinline__ void nset_t(u32 i, u32 t) {
+    if (i < nl) ((lds_u32*)(ndl + i))[1] = t; else ((glb_u32*)(ndg + (i - nl)))[1] = t;
+  }
+  // free list (its head stays in a vector register: the next head's load is not waited for here)
+  u32 fnode, bump;
   __device__ __forceinline__ u32 nalloc() {
-    u32 i;
-    const u32 fn = cget(C_FNODE);
-    if (fn != NIL) {
-      i = fn;
-      cold[C_FNODE] = nget(i).w;
+    u32 i = ufl(fnode);
+    if (i != NIL) {
+      if (i < nl) fnode = ndl[i].w; else fnode = ndg[i - nl].w;
+    } else if (bump < ncap()) {
+      i = bump++;
     } else {
-      const u32 b = cget(C_BUMP);
-      if (b < ncap()) {
-        i = b;
-        cold[C_BUMP] = b + 1;
-      } else {
-        set_status(0x80000000u);  // cannot happen: one node per touch, at most node cap - 2 touches
-        i = 0;
-      }
+      set_status(0x80000000u);  // cannot happen: one node per touch, at most node cap - 2 touches
+      i = 0;
     }
     return i;
+  }
+  __device__ __forceinline__ void nfree(u32 i) {
+    nset_links(i, NIL, fnode);
+    fnode = i;
   }
 
   __device__ __forceinline__ static u32 evictable(u32 n, u32 hold, u32 prot) { return sub0(n, max(hold, prot)); }
 
-  // -- claims: chunks of 64, chunk k in LDS below 256 claims, else in global scratch --
+  // -- claims: chunk 0 (claims 0..63) in registers, one per lane; chunks 1 to 3 in LDS, the rest in
+  //    global scratch --
+  u32x4 q0;  // id | chain << 16, L, T, meta | duration << 16
+  u32x2 x0;  // slot, blocked count
   __device__ __forceinline__ u32x4 cl_ld(u32 base) const {  // this lane's claim of the chunk at base
     u32x4 v;
-    if (base < kClaimsLds) v = cll[base + lane]; else v = clg[base - kClaimsLds + lane];
+    if (base == 0) v = q0; else if (base < kClaimsLds) v = cll[base + lane]; else v = clg[base - kClaimsLds + lane];
     return v;
   }
   __device__ __forceinline__ u32x2 cx_ld(u32 base) const {
     u32x2 v;
-    if (base < kClaimsLds) v = cxl[base + lane]; else v = cxg[base - kClaimsLds + lane];
+    if (base == 0) v = x0; else if (base < kClaimsLds) v = cxl[base + lane]; else v = cxg[base - kClaimsLds + lane];
     return v;
   }
-  __device__ __forceinline__ void cl_set_w(u32 base, u32 w) {  // its meta word (lanes selected by the caller)
-    if (base < kClaimsLds) ((lds_u32*)(cll + base + lane))[3] = w;
-    else ((glb_u32*)(clg + (base - kClaimsLds + lane)))[3] = w;
+  // f(base, claim of this lane, whether it is live) over the chunks
+  template <class Fn>
+  __device__ __forceinline__ void claims(Fn f) const {
+    f(0u, q0, lane < ncl);
+    for (u32 base = 64; __builtin_expect(base < ncl, 0); base += 64) f(base, cl_ld(base), base + lane < ncl);
   }
-  __device__ __forceinline__ void cx_set_blk(u32 base, u32 b) {
-    if (base < kClaimsLds) ((lds_u32*)(cxl + base + lane))[1] = b;
-    else ((glb_u32*)(cxg + (base - kClaimsLds + lane)))[1] = b;
+  // the meta word, or the blocked count, of this lane's claim of a chunk where p holds
+  __device__ __forceinline__ void cl_set_w(u32 base, bool p, u32 w) {
+    if (base == 0) q0.w = p ? w : q0.w;
+    else if (p) {
+      if (base < kClaimsLds) ((lds_u32*)(cll + base + lane))[3] = w;
+      else ((glb_u32*)(clg + (base - kClaimsLds + lane)))[3] = w;
+    }
   }
-  __device__ __forceinline__ void cl_put(u32 j, u32x4 v, u32x2 x) {  // a wave-uniform index
-    if (j < kClaimsLds) { cll[j] = v; cxl[j] = x; } else { clg[j - kClaimsLds] = v; cxg[j - kClaimsLds] = x; }
+  __device__ __forceinline__ void cx_set_blk(u32 base, bool p, u32 b) {
+    if (base == 0) x0.y = p ? b : x0.y;
+    else if (p) {
+      if (base < kClaimsLds) ((lds_u32*)(cxl + base + lane))[1] = b;
+      else ((glb_u32*)(cxg + (base - kClaimsLds + lane)))[1] = b;
+    }
+  }
+  // claim j (wave-uniform)
+  __device__ __forceinline__ void cl_put(u32 j, u32x4 v, u32x2 x) {
+    if (j < 64) {
+      const bool me = lane == j;
+      q0.x = me ? v.x : q0.x; q0.y = me ? v.y : q0.y; q0.z = me ? v.z : q0.z; q0.w = me ? v.w : q0.w;
+      x0.x = me ? x.x : x0.x; x0.y = me ? x.y : x0.y;
+    } else if (j < kClaimsLds) { cll[j] = v; cxl[j] = x; } else { clg[j - kClaimsLds] = v; cxg[j - kClaimsLds] = x; }
   }
   __device__ __forceinline__ u32x4 cl_get(u32 j) const {
     u32x4 v;
-    if (j < kClaimsLds) v = cll[j]; else v = clg[j - kClaimsLds];
-    return ufl4(v);
+    if (j < 64) {
+      v = u32x4{rdl(q0.x, j), rdl(q0.y, j), rdl(q0.z, j), rdl(q0.w, j)};
+    } else {
+      if (j < kClaimsLds) v = cll[j]; else v = clg[j - kClaimsLds];
+      v = ufl4(v);
+    }
+    return v;
   }
   __device__ __forceinline__ u32x2 cx_get(u32 j) const {
     u32x2 v;
-    if (j < kClaimsLds) v = cxl[j]; else v = cxg[j - kClaimsLds];
-    return u32x2{ufl(v.x), ufl(v.y)};
+    if (j < 64) {
+      v = u32x2{rdl(x0.x, j), rdl(x0.y, j)};
+    } else {
+      if (j < kClaimsLds) v = cxl[j]; else v = cxg[j - kClaimsLds];
+      v = u32x2{ufl(v.x), ufl(v.y)};
+    }
+    return v;
   }
   // lane-parallel writes to claims in global scratch reach later reads by other lanes
   __device__ __forceinline__ void cl_fence() {
-    if (ncl > kClaimsLds) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    if (__builtin_expect(ncl > kClaimsLds, 0)) __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
   }
   __device__ __forceinline__ static u32 c_id(u32x4 v) { return v.x & 0xFFFFu; }
@@ -371,21 +441,19 @@ struct Big {
   // soft level of position p of chain c
   __device__ __forceinline__ u32 level_of(u32 c, u32 p) const {
     u32 v = 0;
-    for (u32 base = 0; base < ncl; base += 64) {
-      const u32x4 q = cl_ld(base);
-      const bool on = base + lane < ncl && c_ch(q) == c && leveled(lo16(q.w)) && q.y > p;
+    claims([&](u32, u32x4 q, bool lv) {
+      const bool on = lv && c_ch(q) == c && leveled(lo16(q.w)) && q.y > p;
       v = max(v, on ? m_prio(q.w) + 1u : 0u);
-    }
+    });
     return wmax(v);
   }
   // positions at or above the result have a level <= lvl
   __device__ __forceinline__ u32 level_floor(u32 c, u32 lvl) const {
     u32 v = 0;
-    for (u32 base = 0; base < ncl; base += 64) {
-      const u32x4 q = cl_ld(base);
-      const bool on = base + lane < ncl && c_ch(q) == c && leveled(lo16(q.w)) && m_prio(q.w) + 1u > lvl;
+    claims([&](u32, u32x4 q, bool lv) {
+      const bool on = lv && c_ch(q) == c && leveled(lo16(q.w)) && m_prio(q.w) + 1u > lvl;
       v = max(v, on ? q.y : 0u);
-    }
+    });
     return wmax(v);
   }
 
@@ -395,7 +463,6 @@ struct Big {
     if (g.n > max(g.hold, g.prot)) {
       if (g.nx >= g.n) {
         moved = true;
-        u32 fn = cget(C_FNODE);
         u32 b = g.sbot;
         u32x4 nb = nget(b);
         u32 up = nb.z, nxv = 0;
@@ -404,8 +471,7 @@ struct Big {
           const u32x4 nu = nget(up);
           nxv = nu.x;
           if (nxv >= g.n) {
-            nset_links(b, NIL, fn);  // node b leaves the stack; up becomes the bottom
-            fn = b;
+            nfree(b);  // node b leaves the stack; up becomes the bottom
             b = up;
             nb = nu;
             up = nb.z;
@@ -416,7 +482,6 @@ struct Big {
           }
         }
         nset_links(b, up, NIL);
-        cold[C_FNODE] = fn;
         g.sbot = b;
         g.bt = nb.y;
         g.nx = nxv;
@@ -429,35 +494,46 @@ struct Big {
 
   // Record a touch of positions [0, x) of chain c at step t (x > 0).
   __device__ __forceinline__ void touch(G0& g, u32 x, u32 t) {
-    u32 tp = g.stop, tpd = NIL, reuse = NIL;
+    u32 tp = g.stop, tpd = NIL, reuse = NIL, same = 0;
     bool go = tp != NIL;
     for (u32 guard = 0; go && guard < 0x20000u; guard++) {
       const u32x4 nt = nget(tp);
       tpd = nt.w;
-      if (nt.x <= x) {
+      if (nt.x < x) {
         // the node leaves the stack; the last one to leave becomes the new node
-        if (reuse != NIL) {
-          nset_links(reuse, NIL, cget(C_FNODE));
-          cold[C_FNODE] = reuse;
-        }
+        if (reuse != NIL) nfree(reuse);
         reuse = tp;
         tp = tpd;
         go = tp != NIL;
       } else {
+        same = nt.x == x;
         go = false;
       }
     }
-    const u32 nw = reuse != NIL ? reuse : nalloc();
-    nset(nw, u32x4{x, t, NIL, tp});
-    if (tp != NIL) {
-      nset_links(tp, nw, tpd);
-      if (tp == g.sbot) g.nx = x;
+    u32 st = tp, sb = g.sbot, bt = g.bt, nx = g.nx;
+    if (same) {
+      // the extent is on the stack already (the same prefix touched again): only its step changes
+      nset_t(tp, t);
+      const bool bottom = tp == sb;
+      if (reuse != NIL) {
+        nfree(reuse);
+        nset_links(tp, NIL, tpd);
+        nx = bottom ? 0u : nx;
+      }
+      bt = bottom ? t : bt;
     } else {
-      g.sbot = nw;
-      g.bt = t;
-      g.nx = 0;
+      st = reuse != NIL ? reuse : nalloc();
+      nset(st, u32x4{x, t, NIL, tp});
+      if (tp != NIL) {
+        nset_links(tp, st, tpd);
+        nx = tp == sb ? x : nx;
+      } else {
+        sb = st;
+        bt = t;
+        nx = 0;
+      }
     }
-    g.stop = nw;
+    g.stop = st; g.sbot = sb; g.bt = bt; g.nx = nx;
   }
 
   // Apply new (n, hold, prot) to chain c, optionally touch [0, x) at t, refresh the key and store.
@@ -475,12 +551,11 @@ struct Big {
   // protection extent, and its key.
   __device__ __forceinline__ void recompute(u32 c) {
     u32 pv = 0, cv = 0;
-    for (u32 base = 0; base < ncl; base += 64) {
-      const u32x4 q = cl_ld(base);
-      const bool on = base + lane < ncl && c_ch(q) == c;
+    claims([&](u32, u32x4 q, bool lv) {
+      const bool on = lv && c_ch(q) == c;
       pv = max(pv, on && hardm() && hmat(lo16(q.w)) ? q.y : 0u);
       cv = max(cv, on && !offl(q.w) ? q.y : 0u);
-    }
+    });
     const u32 pp = hardm() ? wmax(pv) : 0u;
     G0 g = rd0(c);
     g.covA = wmax(cv);
@@ -503,10 +578,9 @@ struct Big {
   // Expiry at the start of step t (claims materialized or demoted with a duration).
   __device__ __forceinline__ void expire(u32 t, u32& flags, u32& expired) {
     u32 nx = NEVER, cnt = 0, nf = 0, drop = 0;
-    for (u32 base = 0; base < ncl; base += 64) {
-      const u32x4 q = cl_ld(base);
+    claims([&](u32 base, u32x4 q, bool lv) {
       const u32 m = lo16(q.w), dur = q.w >> 16, st = m_state(m);
-      const bool cand = base + lane < ncl && (st == ST_MATERIALIZED || st == ST_DEMOTED) && dur != 0;
+      const bool cand = lv && (st == ST_MATERIALIZED || st == ST_DEMOTED) && dur != 0;
       const u32 ex = c_id(q) + dur;
       const bool hit = cand && ex <= t;
       nx = min(nx, cand && !hit ? ex : NEVER);
@@ -525,15 +599,15 @@ struct Big {
           nf += (u32)__builtin_popcountll(ballot(fail));
         }
         const u32 slot = cx_ld(base).x;
+        cl_set_w(base, hit, m2 | (dur << 16));
         if (hit) {
-          cl_set_w(base, m2 | (dur << 16));
           rec[slot].w[RW_EXST] = (i32)t;
           if (fail) rec[slot].w[RW_PF] = (i32)t;
         }
         mark_lane(hit, c_ch(q));
         cnt += (u32)__builtin_popcountll(hb);
       }
-    }
+    });
     nexp = wmin(nx);
     expired = cnt;
     if (cnt) {
@@ -550,10 +624,8 @@ struct Big {
   // fails for the first time; a materialized (accepted) claim is harmed (§3.2).
   __device__ __forceinline__ u32 sweep(u32 t) {
     u32 pf = 0, hc = 0;
-    for (u32 base = 0; base < ncl; base += 64) {
-      const u32x4 q = cl_ld(base);
+    claims([&](u32 base, u32x4 q, bool lv) {
       const u32 m = lo16(q.w);
-      const bool lv = base + lane < ncl;
       const u32 c = lv ? c_ch(q) : 0u;
       const bool fail = lv && (m & M_PEND) && chain_n(c) < q.z && !offl(m);
       const u64 fb = ballot(fail);
@@ -561,8 +633,8 @@ struct Big {
         const bool harm = fail && m_state(m) == ST_MATERIALIZED;
         const u32 m2 = (m & ~M_PEND & ~(harm ? 7u : 0u)) | (harm ? ST_HARMED : 0u);
         const u32 slot = cx_ld(base).x;
+        cl_set_w(base, fail, m2 | (q.w & 0xFFFF0000u));
         if (fail) {
-          cl_set_w(base, m2 | (q.w & 0xFFFF0000u));
           rec[slot].w[RW_PF] = (i32)t;
           if (harm) rec[slot].w[RW_HARM] = (i32)t;
         }
@@ -570,7 +642,7 @@ struct Big {
         pf += (u32)__builtin_popcountll(fb);
         hc += (u32)__builtin_popcountll(ballot(harm));
       }
-    }
+    });
     u32 fl = 0;
     if (pf) {
       tadd(TW_PREDFAIL, pf);
@@ -610,22 +682,11 @@ struct Big {
           const u32 m1 = wmin(min(min(k4.x, k4.y), min(k4.z, k4.w)));
           if (!noadm() && fkey < m1) {
             // the oldest finished request's private run (level 0)
-            const u32 flo = cget(C_FLO), ftop = cget(C_FTOP);
             const u32 m = min(K, ftop - flo);
             E -= m;
             K -= m;
-            cold[C_FTOP] = ftop - m;
-            if (ftop - m == flo) {
-              const u32 qh = cget(C_QH) + 1;
-              cold[C_QH] = qh;
-              fkey = KINF;
-              if (qh != cget(C_QT)) {
-                const u32x4 e = ufl4(fifo[qh]);
-                fkey = e.x << 9;
-                cold[C_FLO] = e.y;
-                cold[C_FTOP] = e.z;
-              }
-            }
+            ftop -= m;
+            if (ftop == flo) fifo_pop();
           } else if (m1 != KINF) {
             const u32 c = (m1 & 511u) - 1u;
             G0 g = rd0(c);
@@ -641,14 +702,13 @@ struct Big {
             if (g.covA > nw) {
               // victims inside live claims: resident; inside only demoted / expired ones: post-release
               u32 cv = 0, due = 0;
-              for (u32 base = 0; base < ncl; base += 64) {
-                const u32x4 q = cl_ld(base);
+              claims([&](u32, u32x4 q, bool lv) {
                 const u32 st = m_state(q.w);
-                const u32 on = (u32)(base + lane < ncl) & (u32)(c_ch(q) == c) & (u32)!offl(q.w);
+                const u32 on = (u32)lv & (u32)(c_ch(q) == c) & (u32)!offl(q.w);
                 // observed (1), materialized (2) or harmed (6)
                 cv = max(cv, (on & (0x46u >> st) & 1u) ? q.y : 0u);
                 due |= on & (u32)((q.w & M_PEND) != 0) & (u32)(q.z > nw);
-              }
+              });
               const u32 covS = wmax(cv);
               const u32 rs = min(nn, g.covA) - nw;
               r.resident += rs;
@@ -691,21 +751,18 @@ struct Big {
     if (hardm() && Pr > 0 && req <= U()) {
       o.code = RKC_OC_REFUSED_CLAIM;
       u32 mn = NEVER, nb = 0;
-      for (u32 base = 0; base < ncl; base += 64) {
-        const u32x4 q = cl_ld(base);
-        const bool lv = base + lane < ncl;
+      claims([&](u32 base, u32x4 q, bool lv) {
         const u32 c = lv ? c_ch(q) : 0u;
         u32 cov = chain_hold(c);
         if ((i32)c == hc) cov = max(cov, h);
         const bool blk = lv && hmat(lo16(q.w)) && q.y > cov;
         const u64 bb = ballot(blk);
         if (bb) {
-          const u32 n = cx_ld(base).y;
-          if (blk) cx_set_blk(base, n + 1u);
+          cx_set_blk(base, blk, cx_ld(base).y + 1u);
           nb += (u32)__builtin_popcountll(bb);
           mn = min(mn, blk ? c_id(q) : NEVER);
         }
-      }
+      });
       o.id = (i32)wmin(mn);
       o.n16 = min(nb, 65535u);
       cl_fence();
@@ -732,10 +789,7 @@ struct Big {
   // Largest footprint of the materialized hard claims on chain c.
   __device__ __forceinline__ u32 hard_extent(u32 c) const {
     u32 v = 0;
-    for (u32 base = 0; base < ncl; base += 64) {
-      const u32x4 q = cl_ld(base);
-      v = max(v, base + lane < ncl && c_ch(q) == c && hmat(lo16(q.w)) ? q.y : 0u);
-    }
+    claims([&](u32, u32x4 q, bool lv) { v = max(v, lv && c_ch(q) == c && hmat(lo16(q.w)) ? q.y : 0u); });
     return wmax(v);
   }
 
@@ -760,9 +814,7 @@ struct Big {
         bool go = true;
         for (u32 guard = 0; go && need > avail && guard <= ncl; guard++) {
           u32 best = NEVER, bj = 0;
-          for (u32 base = 0; base < ncl; base += 64) {
-            const u32x4 q = cl_ld(base);
-            const bool lv = base + lane < ncl;
+          claims([&](u32 base, u32x4 q, bool lv) {
             const u32 c = lv ? c_ch(q) : 0u;
             u32 cov = chain_hold(c);
             if ((i32)c == hc) cov = max(cov, h);
@@ -770,7 +822,7 @@ struct Big {
             const bool cand = lv && hmat(lo16(q.w)) && (q.w & (M_DEMQ | M_OFFQ)) && q.y > cov && key >= from && key < best;
             best = cand ? key : best;
             bj = cand ? base + lane : bj;
-          }
+          });
           const u32 wb = wmin(best);
           if (wb == NEVER) {
             go = false;
@@ -796,21 +848,21 @@ struct Big {
           }
         }
         const bool fits = need <= avail;
-        for (u32 base = 0; k > 0 && base < ncl; base += 64) {
-          const u32x2 x = cx_ld(base);
-          if (base + lane < ncl && (x.y & kPicked)) {
-            const u32x4 q = cl_ld(base);
+        if (k > 0) {
+          claims([&](u32 base, u32x4 q, bool lv) {
+            const u32x2 x = cx_ld(base);
+            const bool p = lv && (x.y & kPicked);
             const u32 m = lo16(q.w);
             const bool off = m_eff(m) == RKC_PROT_OFFLOADED;
-            cx_set_blk(base, x.y & ~kPicked);
+            cx_set_blk(base, p, x.y & ~kPicked);
             if (fits) {
-              if (!off) rec[x.x].w[RW_DEM] = (i32)t;
+              if (p && !off) rec[x.x].w[RW_DEM] = (i32)t;
             } else {
               const u32 m2 = (off ? (m & ~(3u << 3)) | (RKC_PROT_HARD << 3) : (m & ~7u) | ST_MATERIALIZED) & ~M_RELAXED;
-              cl_set_w(base, m2 | (q.w & 0xFFFF0000u));
+              cl_set_w(base, p, m2 | (q.w & 0xFFFF0000u));
             }
-            mark_lane(fits, c_ch(q));
-          }
+            mark_lane(p && fits, c_ch(q));
+          });
         }
         if (k) cl_fence();
         if (fits) {
@@ -833,11 +885,13 @@ struct Big {
   }
   static constexpr u32 kPicked = 1u << 31;
   __device__ __forceinline__ void cx_put_blk(u32 j, u32 b) {
-    if (j < kClaimsLds) ((lds_u32*)(cxl + j))[1] = b;
+    if (j < 64) x0.y = lane == j ? b : x0.y;
+    else if (j < kClaimsLds) ((lds_u32*)(cxl + j))[1] = b;
     else ((glb_u32*)(cxg + (j - kClaimsLds)))[1] = b;
   }
   __device__ __forceinline__ void cl_put_w(u32 j, u32 w) {
-    if (j < kClaimsLds) ((lds_u32*)(cll + j))[3] = w;
+    if (j < 64) q0.w = lane == j ? w : q0.w;
+    else if (j < kClaimsLds) ((lds_u32*)(cll + j))[3] = w;
     else ((glb_u32*)(clg + (j - kClaimsLds)))[3] = w;
   }
 
@@ -845,10 +899,11 @@ struct Big {
   // retried request, inserted into the live list by id and taken off the deferral ring (dh, dl).
   __device__ __forceinline__ void admit(u32 t, u32 rid, u32 S, u32 cc, u32 P, bool late, u32 dh, u32 dl, Out& o) {
     i32 hc = -1;
-    u32 h = 0, Hc = 0;
+    u32 h = 0, Hc = 0, hk = 0;
     G0 g = {0, 0, 0, 0, 0, 0, 0, 0};
     if (P > 0) {
       hc = (i32)cc;
+      hk = hcnt[cc];
       g = rd0(cc);
       h = min(P, g.n);
       Hc = sub0(h, g.hold);
@@ -888,7 +943,7 @@ struct Big {
         R = noadm() ? h : P;
         const u32 nn = (!noadm() && P > g2.n) ? P : g2.n;
         // (the chain's hold is the largest R of its live requests; hcnt counts those holding it)
-        if (R > 0 && R >= g2.hold) hcnt[cc] = R > g2.hold ? 1u : ufl(hcnt[cc]) + 1u;
+        if (R > 0 && R >= g2.hold) hcnt[cc] = R > g2.hold ? 1u : hk + 1u;
         commit(cc, g2, nn, max(g2.hold, R), g2.prot, R, t);
       }
       const u32x2 e = rq_pack(rid, hc >= 0 ? cc : 0u, R, S);
@@ -907,10 +962,9 @@ struct Big {
       if (ext() && P > h && t2cap() > 0) {
         // positions past the hits that a claim holding a second-tier copy covers are restored
         u32 ev = 0;
-        for (u32 base = 0; base < ncl; base += 64) {
-          const u32x4 q = cl_ld(base);
-          ev = max(ev, base + lane < ncl && c_ch(q) == cc && m_eff(q.w) == RKC_PROT_OFFLOADED ? q.y : 0u);
-        }
+        claims([&](u32, u32x4 q, bool lv) {
+          ev = max(ev, lv && c_ch(q) == cc && m_eff(q.w) == RKC_PROT_OFFLOADED ? q.y : 0u);
+        });
         tadd(TW_RESTORED, sub0(min(P, wmax(ev)), h));
       }
     }
@@ -1029,14 +1083,18 @@ struct Big {
       const u32x2 e = u32x2{ufl(e0.x), ufl(e0.y)};
       const u32 rid = rq_id(e), c = rq_c(e), R = rq_R(e), len = rq_len(e);
       G0 g;
-      if (R > 0) g = rd0(c);
+      u32 hk = 0;
+      if (R > 0) {
+        hk = hcnt[c];
+        g = rd0(c);
+      }
       rq_remove(i);
       u32 turned = 0;
       if (R > 0) {
         // the hold falls only when the last request that held it finishes
         u32 hn = g.hold;
         if (R == hn) {
-          const u32 hk = ufl(hcnt[c]);
+          hk = ufl(hk);
           if (hk > 1) {
             hcnt[c] = hk - 1;
           } else {
@@ -1054,16 +1112,7 @@ struct Big {
       turned += kept;
       F += dropped;
       E += kept;
-      if (kept > 0) {
-        const u32 qt = cget(C_QT);
-        if (fkey == KINF) {
-          fkey = t << 9;
-          cold[C_FLO] = R;
-          cold[C_FTOP] = len;
-        }
-        fifo[qt] = u32x4{t, R, len, 0u};  // every lane, one value
-        cold[C_QT] = qt + 1;
-      }
+      if (kept > 0) fifo_push(t, R, len);
       peak = max(peak, A);  // (A only falls here)
       A -= turned + dropped;
       o.code = RKC_OC_FINISHED;
@@ -1086,15 +1135,27 @@ struct Big {
 
   // Claims [i + 1, ncl) move down one place.
   __device__ __forceinline__ void cl_remove(u32 i) {
-    for (u32 base = i & ~63u; base < ncl; base += 64) {
-      // this chunk's entries from i on take their successor's value; the last lane's successor is the
-      // first entry of the next chunk
+    if (i < 64) {
+      const bool up = lane >= i;
+      q0.x = up ? shift_down(q0.x) : q0.x; q0.y = up ? shift_down(q0.y) : q0.y;
+      q0.z = up ? shift_down(q0.z) : q0.z; q0.w = up ? shift_down(q0.w) : q0.w;
+      x0.x = up ? shift_down(x0.x) : x0.x; x0.y = up ? shift_down(x0.y) : x0.y;
+      if (__builtin_expect(ncl > 64, 0)) {
+        const u32x4 v = cl_get(64);
+        const u32x2 x = cx_get(64);
+        cl_put(63, v, x);
+      }
+    }
+    const u32 from = max(i, 64u);
+    for (u32 base = from & ~63u; __builtin_expect(base < ncl, 0); base += 64) {
+      // this chunk's entries from `from` on take their successor's value; the last lane's successor is
+      // the first entry of the next chunk
       const u32 j = base + lane, src = min(j + 1, ncl - 1);
       u32x4 v;
       u32x2 x;
       if (src < kClaimsLds) { v = cll[src]; x = cxl[src]; } else { v = clg[src - kClaimsLds]; x = cxg[src - kClaimsLds]; }
       __builtin_amdgcn_wave_barrier();
-      if (j >= i && j + 1 < ncl) {
+      if (j >= from && j + 1 < ncl) {
         if (base < kClaimsLds) { cll[j] = v; cxl[j] = x; } else { clg[j - kClaimsLds] = v; cxg[j - kClaimsLds] = x; }
       }
       __builtin_amdgcn_wave_barrier();
@@ -1212,7 +1273,7 @@ __device__ __forceinline__ void replay_pool(const rkc_big_args& g, const rkc_poo
   P.nl = g.nodes_lds;
   unsigned char* scr = (unsigned char*)g.scratch + (u64)pool * g.scr_pool_bytes;
   P.ndg = (glb_u32x4*)(scr + g.scr_off_nodes);
-  P.fifo = (glb_u32x4*)(scr + g.scr_off_fifo);
+  P.fifo = (glb_u32x2*)(scr + g.scr_off_fifo);
   P.slot2 = (glb_u32x2*)(scr + g.scr_off_slots);
   P.dq = (glb_u32x4*)(scr + g.scr_off_defer);
   P.clg = (glb_u32x4*)(scr + g.scr_off_claims);
@@ -1225,11 +1286,14 @@ __device__ __forceinline__ void replay_pool(const rkc_big_args& g, const rkc_poo
     P.ch[2 * c + 1] = u32x4{0, 0, NIL, NIL};
   }
   if (l < 16) { P.hist[l] = 0; P.mark[l] = 0; }
-  if (l < BP::C_WORDS) P.cold[l] = l == BP::C_FNODE ? NIL : l == BP::C_DQC ? 1u : 0u;
+  if (l < BP::C_WORDS) P.cold[l] = l == BP::C_DQC ? 1u : 0u;
+  P.q0 = u32x4{0, 0, 0, 0};
+  P.x0 = u32x2{0, 0};
   P.tv = 0;
   P.F = U; P.A = 0; P.PR = 0; P.peak = 0; P.E = 0;
   P.nreq = 0; P.ncl = 0; P.nexp = NEVER; P.sweep_due = 0; P.vic = 0; P.post = 0; P.nslot = 0;
-  P.fkey = KINF;
+  P.qh = P.qt = P.flo = P.ftop = 0; P.fkey = KINF; P.fnext = u32x2{0, 0};
+  P.fnode = NIL; P.bump = 0;
   __syncthreads();
 
   const rkc_event* __restrict__ ev = g.events + d.event_offset;
@@ -1367,7 +1431,7 @@ bool rkc_big_layout(const rkc_batch* b, rkc_big_args* g) {
   u64 s = 0;
   auto take = [&](u64 bytes) { const u64 r = s; s = align_up(s + bytes, 256); return r; };
   g->scr_off_nodes = take(16ull * (g->node_cap - g->nodes_lds));
-  g->scr_off_fifo = take(16ull * ((u64)b->max_events + 1));
+  g->scr_off_fifo = take(8ull * ((u64)b->max_events + 1));
   g->scr_off_slots = take(8ull * (u64)(b->max_claim_slots > 0 ? b->max_claim_slots : 1));
   g->scr_off_defer = take(16ull * reqs);
   g->scr_off_claims = take(claims > kClaimsLds ? 16ull * align_up(claims - kClaimsLds, 64) : 0);

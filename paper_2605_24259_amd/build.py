@@ -3,16 +3,18 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-SRCS = [os.path.join(PKG, "csrc", f) for f in ("rkc_replay.hip", "rkc_lean.hip", "rkc_big.hip",
-                                              "rkc_tiny.hip")]
+SRCS = [os.path.join(PKG, "csrc", f) for f in ("rkc_replay.hip", "rkc_lean.hip", "rkc_lean_few.hip",
+                                              "rkc_big.hip", "rkc_tiny.hip")]
 LIB = os.path.join(PKG, "librkc.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "-shared", f"--offload-arch={ARCH}",
+    "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
     # packed FP32 instructions are kept off for all device code on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # Leave regions whose branches are wave-uniform unstructured.  The per-pool event loops branch
@@ -38,10 +40,17 @@ CHECK_LIB = os.path.join(PKG, "librkc_check.so")
 def build(verbose: bool = False, check_uniform: bool = False) -> str:
     out = CHECK_LIB if check_uniform else LIB
     tmp = out + ".tmp%d" % os.getpid()
-    cmd = [hipcc(), *HIPCC_FLAGS, *(["-DRKC_CHECK_UNIFORM"] if check_uniform else []), *SRCS, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    flags = [hipcc(), *HIPCC_FLAGS, *(["-DRKC_CHECK_UNIFORM"] if check_uniform else [])]
+    with tempfile.TemporaryDirectory() as d:
+        objs = [os.path.join(d, os.path.basename(f) + ".o") for f in SRCS]
+        cmds = [[*flags, "-c", f, "-o", o] for f, o in zip(SRCS, objs)]
+        link = [hipcc(), "-shared", f"--offload-arch={ARCH}", *objs, "-o", tmp]
+        if verbose:
+            print("\n".join(" ".join(c) for c in [*cmds, link]), flush=True)
+        # the sources are independent: one compiler each, side by side
+        with ThreadPoolExecutor(min(len(cmds), os.cpu_count() or 1)) as pool:
+            list(pool.map(subprocess.check_call, cmds))
+        subprocess.check_call(link)
     os.replace(tmp, out)
     return out
 

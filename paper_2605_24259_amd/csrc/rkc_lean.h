@@ -19,6 +19,7 @@ struct rkc_lean_args {
   int32_t n_pools, max_usable, max_events, max_chains, max_reqs, max_claims, max_slots;
   // layout: LDS byte offsets, node split, per-pool scratch regions
   uint32_t ordered;  // the launch groups the pools by event loop
+  uint32_t few;      // the layout for few pools: all live requests, more nodes in LDS
   uint32_t ns, nq, node_cap, nodes_lds;  // 64-chain key groups, 64-claim sets, node split
   uint32_t lds_bytes;  // LDS per pool (its regions sit at offsets fixed per kernel instantiation)
   uint64_t scr_pool_bytes, scr_off_nodes, scr_off_fifo, scr_off_slots, scr_off_defer, scr_off_reqs;
@@ -34,6 +35,9 @@ bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g);
 // Launch the compact kernel (one 64-lane workgroup per pool) on stream s.
 rkc_status rkc_lean_launch(const rkc_lean_args* g, hipStream_t s);
 
+// Its replay of a batch with g->few set (rkc_lean_few.hip).
+rkc_status rkc_lean_few_replay(const rkc_lean_args* g, hipStream_t s);
+
 // Batches of short traces: a lane replays a pool (rkc_tiny.hip).
 bool rkc_tiny_fits(const rkc_lean_args* g);
 rkc_status rkc_tiny_launch(const rkc_lean_args* g, hipStream_t s);
@@ -41,6 +45,7 @@ rkc_status rkc_tiny_launch(const rkc_lean_args* g, hipStream_t s);
 #ifdef RKC_CHECK_UNIFORM
 // checking build only: calls of the compact kernel's readfirstlane whose active lanes disagreed
 unsigned rkc_lean_uniform_violations(void);
+unsigned rkc_lean_few_uniform_violations(void);
 #endif
 
 #endif

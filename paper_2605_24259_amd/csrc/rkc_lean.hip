@@ -182,17 +182,17 @@ struct AllocRes {
 // bound the chains (64 NS) and the live requests kept in LDS; with one claim set the LDS a pool
 // takes sets how many pools share a CU (the CU allocates LDS in 1,280-byte units), with four the
 // registers set it.
-template <int NS, int NQ>
+template <int NS, int NQ, bool FEW>
 struct LdsMap {
   // live requests in LDS: a zipf pool that allows 256 live requests holds ~50 on average and 165 at
   // most, so with one claim set the first 128 (96 with 256 chains) stay in LDS and the rest go to
   // global scratch
-  static constexpr u32 RQL = NQ == 4 ? 256u : NS == 4 ? 96u : 128u;
+  static constexpr u32 RQL = FEW || NQ == 4 ? 256u : NS == 4 ? 96u : 128u;
   // touch-stack nodes in LDS (a zipf pool of 256 chains peaks at ~80-115 live nodes, the 80-block
   // pools at ~35): with 256 chains 48, which brings a pool to 6,400 B, five allocation units, so 25
   // pools share a CU instead of 21 (more than paying for the slower node accesses); of those five
   // units, 96 requests and 48 nodes measured faster than 128 and 16 or 64 and 80
-  static constexpr u32 NL = NS == 4 ? 48u : 64u;
+  static constexpr u32 NL = FEW ? 256u : NS == 4 ? 48u : 64u;
   static constexpr u32 COLD = 0, HIST = 64, KEYS = 128, CH = KEYS + 256u * NS, RQ = CH + 1024u * NS,
                        ND = RQ + 8u * RQL, BYTES = ND + 8u * NL;
 };
@@ -202,7 +202,7 @@ struct LdsMap {
 // j mod 64 of set j / 64); MODE: the pool policy, fixed at compile time so that each policy's event
 // loop carries only the logic that policy can reach; EXT: a hard-protection pool that defers or
 // relaxes, whose loop carries the deferral ring and the runtime relaxation.
-template <int NS, int NQ, int MODE, bool EXT>
+template <int NS, int NQ, int MODE, bool EXT, bool FEW>
 struct Lean {
   static constexpr u32 KC = 64u * NS;  // key slots (chains padded to whole lanes)
   // descriptor: the rarely used limits one per lane of `cst`
@@ -234,7 +234,7 @@ struct Lean {
   lds_u32* hist;  // outcomes per code (16 counters; entry 15 collects the lanes past the end)
   lds_u32x4* ch;
   // live requests: entries [0, RQL) in LDS, the rest in global scratch
-  static constexpr u32 RQL = LdsMap<NS, NQ>::RQL;
+  static constexpr u32 RQL = LdsMap<NS, NQ, FEW>::RQL;
   lds_u32x2* rq;
   glb_u32x2* rqg;
   // (per-lane j; L: the caller knows every index it uses lies in LDS, so no lane-dependent branch
@@ -279,7 +279,7 @@ struct Lean {
   lds_u32x2* ndl;
   glb_u32x2* ndg;
   // nodes [0, NL) in LDS, the rest in global scratch
-  static constexpr u32 NL = LdsMap<NS, NQ>::NL;
+  static constexpr u32 NL = LdsMap<NS, NQ, FEW>::NL;
   glb_u32x2* fifo;  // finished requests' private runs: finish step | low end << 16, top (16-bit fields)
   glb_u32x4* dq;  // deferred requests: PREFILL step, S, chain, P
   // Claim records.  A live claim's words 0..8 are written by its own lane when it is released or at
@@ -322,12 +322,18 @@ struct Lean {
   enum : u32 { C_QH = 0, C_QT, C_FKEY, C_FLO, C_FTOP, C_FNODE, C_BUMP, C_STATUS,
                C_DQH, C_DQL, C_DQC, C_T2, C_T2PK, C_WORDS };
   static_assert(C_QH % 4 == 0 && C_DQH % 2 == 0 && C_DQL == C_DQH + 1 && C_WORDS <= 16, "cold block layout");
+  // (few pools: in registers throughout, and with them the run behind the front one, loaded ahead,
+  // and the node free-list head, in a vector register so that the next head's load is not waited for)
   u32 qh, qt, fk, flo, ftop;    // valid between cold_fifo_in() and cold_fifo_out()
+  u32x2 fnext;
+  u32 fnode;
   __device__ __forceinline__ void cold_fifo_in() {
+    if (FEW) return;
     const u32x4 v = *(lds_u32x4*)(cold + C_QH);  // QH, QT, FKEY, FLO
     qh = ufl(v.x); qt = ufl(v.y); fk = ufl(v.z); flo = ufl(v.w); ftop = ufl(cold[C_FTOP]);
   }
   __device__ __forceinline__ void cold_fifo_out() {
+    if (FEW) return;
     *(lds_u32x4*)(cold + C_QH) = u32x4{qh, qt, fk, flo};
     cold[C_FTOP] = ftop;
   }
@@ -372,12 +378,22 @@ struct Lean {
   }
   // (the free list head and the bump pointer are read and written in the cold block where they
   // are needed: a touch that reuses a popped node needs neither)
+  __device__ __forceinline__ u32 free_head() const { return FEW ? ufl(fnode) : ufl(cold[C_FNODE]); }
+  __device__ __forceinline__ void set_free_head(u32 i) {
+    if (FEW) fnode = i; else cold[C_FNODE] = i;
+  }
   __device__ __forceinline__ u32 nalloc() {
     u32 i;
-    const u32 fn = ufl(cold[C_FNODE]);
+    const u32 fn = free_head();
     if (fn != NIL) {
       i = fn;
-      cold[C_FNODE] = hi16(nget(i).y);
+      if (!FEW) {
+        cold[C_FNODE] = hi16(nget(i).y);
+      } else {
+        u32 y;
+        if (i < NL) y = ndl[i].y; else y = ndg[i - NL].y;
+        fnode = hi16(y);
+      }
     } else {
       const u32 b = ufl(cold[C_BUMP]);
       if (b < ncap()) {
@@ -442,7 +458,7 @@ struct Lean {
       if (g.nx >= g.n) {
         moved = true;
         // (rare: the node free list is read and written here, not kept in registers around it)
-        u32 fn = ufl(cold[C_FNODE]);
+        u32 fn = free_head();
         u32 b = g.sbot;
         u32x2 nb = nget(b);
         u32 up = lo16(nb.y), nxv = 0;
@@ -464,7 +480,7 @@ struct Lean {
           }
         }
         nset_y(b, pk(up, NIL));
-        cold[C_FNODE] = fn;
+        set_free_head(fn);
         g.sbot = b;
         g.bt = hi16(nb.x);
         g.nx = nxv;
@@ -488,8 +504,8 @@ struct Lean {
         // the node leaves the stack; the last one to leave becomes the new node, the others go to
         // the free list
         if (reuse != NIL) {
-          nset_y(reuse, pk(NIL, ufl(cold[C_FNODE])));
-          cold[C_FNODE] = reuse;
+          nset_y(reuse, pk(NIL, free_head()));
+          set_free_head(reuse);
         }
         reuse = tp;
         tp = tpd;
@@ -637,9 +653,11 @@ struct Lean {
     qh++;
     fk = KINF;
     if (qh != qt) {
-      const u32x2 e = *gat(fifo, qh);
+      u32x2 e;
+      if (FEW) e = fnext; else e = *gat(fifo, qh);
       const u32 x = ufl(e.x);
       fk = lo16(x) << 9; flo = hi16(x); ftop = ufl(e.y);
+      if (FEW && qh + 1 != qt) fnext = *gat(fifo, qh + 1);
     }
   }
 
@@ -670,7 +688,7 @@ struct Lean {
         const u32 K0 = K;
         vic += K;
         // the front private run's key (the rest of the FIFO state is read when a run is taken)
-        u32 kf = noadm() ? KINF : ufl(cold[C_FKEY]);
+        u32 kf = noadm() ? KINF : FEW ? fk : ufl(cold[C_FKEY]);
         // the hit chain stops being a candidate once only hits remain
         if (hc >= 0 && ghc.n <= hlo) kk[vx(hc)] = KINF;
         for (u32 guard = 0; K > 0; guard++) {
@@ -1192,8 +1210,10 @@ struct Lean {
       E += kept;
       if (kept > 0) {
         cold_fifo_in();
+        const u32x2 e = u32x2{pk(t, R), len};
         if (qh == qt) { fk = t << 9; flo = R; ftop = len; }
-        *gat(fifo, qt) = u32x2{pk(t, R), len};  // every lane, one value
+        else if (FEW && qh + 1 == qt) fnext = e;
+        *gat(fifo, qt) = e;  // every lane, one value
         qt++;
         cold_fifo_out();
       }
@@ -1337,10 +1357,10 @@ struct Lean {
 };
 
 // Replay of one pool with policy MODE (the descriptor has been checked by the caller).
-template <int NS, int NQ, int MODE, bool EXT>
+template <int NS, int NQ, int MODE, bool EXT, bool FEW>
 __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_pool_desc& d, u32 pool,
                                             unsigned char* lds_raw, const rkc_event* __restrict__ evs) {
-  typedef Lean<NS, NQ, MODE, EXT> LP;
+  typedef Lean<NS, NQ, MODE, EXT, FEW> LP;
   LP P;
   P.lane = __lane_id();
   const i64 ev_off = d.event_offset, slot_off = d.claim_slot_offset;
@@ -1355,7 +1375,7 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
   const u32 U = (u32)d.usable_blocks, nch = (u32)d.n_chains, nslots = (u32)d.n_claim_slots;
 
   lds_u32* lds = (lds_u32*)lds_raw;
-  typedef LdsMap<NS, NQ> M;
+  typedef LdsMap<NS, NQ, FEW> M;
   P.kk = lds + M::KEYS / 4;
   P.ch = (lds_u32x4*)(lds + M::CH / 4);
   P.rq = (lds_u32x2*)(lds + M::RQ / 4);
@@ -1383,18 +1403,24 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
   P.cold = lds + M::COLD / 4;
   if (P.lane < LP::C_WORDS)
     P.cold[P.lane] = P.lane == LP::C_FNODE ? NIL : P.lane == LP::C_DQC ? 1u : P.lane == LP::C_FKEY ? KINF : 0u;
+  if (FEW) {
+    P.qh = P.qt = P.flo = P.ftop = 0; P.fk = KINF; P.fnext = u32x2{0, 0}; P.fnode = NIL;
+  }
   __syncthreads();
 
   const rkc_event* __restrict__ ev = evs + ev_off;
   rkc_outcome* out = g.outcomes + ev_off;
   const u32 ne = (u32)d.n_events;
+  int4 ahead = make_int4(0, 0, 0, 0);  // few pools: the next tile's events, loaded while this one runs
+  if (FEW && P.lane < ne) ahead = *(const int4*)(ev + P.lane);
   for (u32 base = 0; base < ne; base += 64) {
     const u32 cnt = min(64u, ne - base);
     u32 e0 = 0, e1 = 0, e2 = 0, e3 = 0;
     if (P.lane < cnt) {
-      const int4 x = *(const int4*)(ev + base + P.lane);
+      const int4 x = FEW ? ahead : *(const int4*)(ev + base + P.lane);
       e0 = (u32)x.x; e1 = (u32)x.y; e2 = (u32)x.z; e3 = (u32)x.w;
     }
+    if (FEW && base + 64 + P.lane < ne) ahead = *(const int4*)(ev + base + 64 + P.lane);
     const u32 badv = P.malformed(e0, e1, e2, e3);
     // outcome fields of event k go to lane k; the words are assembled for the tile at once
     u32 vcode = 0, vflags = 0, vn16 = 0, vid = 0, va = 0, vb = 0;
@@ -1405,7 +1431,9 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
       // checks; a 32-bit byte offset to the tile's base keeps the address a single shift; the
       // event's malformed flag is read from its lane, one vector instruction in place of a 64-bit
       // scalar shift and a mask)
-      const int4 xe = *(const int4*)((const char*)(ev + base) + (k << 4));
+      // (few pools wait for that load, so there the words come from the lanes)
+      const int4 xe = FEW ? make_int4((i32)rdl(e0, k), (i32)rdl(e1, k), (i32)rdl(e2, k), (i32)rdl(e3, k))
+                          : *(const int4*)((const char*)(ev + base) + (k << 4));
       P.step(base + k, (u32)xe.x, (u32)xe.y, (u32)xe.z, (u32)xe.w, rdl(badv, k), o);
       vcode = wrl(vcode, o.code, k); vflags = wrl(vflags, o.flags, k); vn16 = wrl(vn16, o.n16, k);
       vid = wrl(vid, (u32)o.id, k); va = wrl(va, (u32)o.a, k); vb = wrl(vb, (u32)o.b, k);
@@ -1473,6 +1501,7 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
   }
 }
 
+#ifndef RKC_LEAN_FEW
 // Event loop a pool runs: 0 hard protection with deferral or relaxation, 1 hard, 2 soft, 3 native,
 // 4 no-admit, 5 a descriptor the replay rejects (heaviest loops first).
 __device__ __forceinline__ u32 loop_class(const rkc_pool_desc& d) {
@@ -1544,14 +1573,16 @@ __global__ __launch_bounds__(1024) void rkc_lean_order_scatter(i32 n_pools, cons
   }
 }
 
+#endif  // RKC_LEAN_FEW
+
 // One wavefront per pool, in the launch order above (or batch order); the pool's policy selects its
 // specialized event loop once.  With four claim sets the registers, not LDS, bound residency: the kernel is
 // held to 6 waves per SIMD (80 vector registers, a few values spilled to scratch; 5 waves and 93
 // registers otherwise, measured slower: nested 9.9 vs 9.3 ms).
-template <int NS, int NQ>
+template <int NS, int NQ, bool FEW>
 // (the events come as a separate restrict-qualified argument as well, so that the compiler knows no
 // store of the replay reaches them and may read them through the scalar cache)
-__global__ __launch_bounds__(64, NQ > 1 ? 6 : 1) void rkc_lean(rkc_lean_args g, const rkc_event* __restrict__ evs) {
+__global__ __launch_bounds__(64, !FEW && NQ > 1 ? 6 : 1) void rkc_lean(rkc_lean_args g, const rkc_event* __restrict__ evs) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   if ((i32)blockIdx.x >= g.n_pools) return;
   const u32 pool = g.ordered ? ((const u32*)((const unsigned char*)g.scratch + g.scr_off_order))[blockIdx.x] : blockIdx.x;
@@ -1579,16 +1610,39 @@ __global__ __launch_bounds__(64, NQ > 1 ? 6 : 1) void rkc_lean(rkc_lean_args g, 
   }
   const u32 mode = (u32)__builtin_amdgcn_readfirstlane(d.mode & ~RKC_MODE_RELAX);
   const u32 ext = (u32)__builtin_amdgcn_readfirstlane(d.defer_limit) > 0 || (d.mode & RKC_MODE_RELAX);
-  if (mode == RKC_MODE_LRU) replay_pool<NS, NQ, RKC_MODE_LRU, false>(g, d, pool, lds_raw, evs);
-  else if (mode == RKC_MODE_SOFT) replay_pool<NS, NQ, RKC_MODE_SOFT, false>(g, d, pool, lds_raw, evs);
-  else if (mode == RKC_MODE_NOADMIT) replay_pool<NS, NQ, RKC_MODE_NOADMIT, false>(g, d, pool, lds_raw, evs);
-  else if (!ext) replay_pool<NS, NQ, RKC_MODE_HARD, false>(g, d, pool, lds_raw, evs);
-  else replay_pool<NS, NQ, RKC_MODE_HARD, true>(g, d, pool, lds_raw, evs);
+  if (mode == RKC_MODE_LRU) replay_pool<NS, NQ, RKC_MODE_LRU, false, FEW>(g, d, pool, lds_raw, evs);
+  else if (mode == RKC_MODE_SOFT) replay_pool<NS, NQ, RKC_MODE_SOFT, false, FEW>(g, d, pool, lds_raw, evs);
+  else if (mode == RKC_MODE_NOADMIT) replay_pool<NS, NQ, RKC_MODE_NOADMIT, false, FEW>(g, d, pool, lds_raw, evs);
+  else if (!ext) replay_pool<NS, NQ, RKC_MODE_HARD, false, FEW>(g, d, pool, lds_raw, evs);
+  else replay_pool<NS, NQ, RKC_MODE_HARD, true, FEW>(g, d, pool, lds_raw, evs);
 }
 
-u64 align_up(u64 v, u64 a) { return (v + a - 1) / a * a; }
-
 }  // namespace
+
+template <int NS, int NQ, bool FEW>
+static rkc_status replay(const rkc_lean_args* g, hipStream_t s) {
+  hipLaunchKernelGGL((rkc_lean<NS, NQ, FEW>), dim3((unsigned)g->n_pools), dim3(64), g->lds_bytes, s, *g, g->events);
+  return hipGetLastError() == hipSuccess ? RKC_OK : RKC_E_HIP;
+}
+
+#ifdef RKC_LEAN_FEW
+
+rkc_status rkc_lean_few_replay(const rkc_lean_args* g, hipStream_t s) {
+  if (g->nq == 4) return g->ns == 1 ? replay<1, 4, true>(g, s) : replay<4, 4, true>(g, s);
+  return g->ns == 1 ? replay<1, 1, true>(g, s) : replay<4, 1, true>(g, s);
+}
+
+#ifdef RKC_CHECK_UNIFORM
+unsigned rkc_lean_few_uniform_violations(void) {
+  unsigned v = 0;
+  if (hipMemcpyFromSymbol(&v, HIP_SYMBOL(g_lean_uniform_violations), sizeof v) != hipSuccess) return ~0u;
+  return v;
+}
+#endif
+
+#else  // RKC_LEAN_FEW
+
+static u64 align_up(u64 v, u64 a) { return (v + a - 1) / a * a; }
 
 // Layout of the compact kernel for batch b, or false when the batch is outside its limits.
 bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g) {
@@ -1600,7 +1654,7 @@ bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g) {
       b->max_live_claims > 256 || b->max_live_requests > 256 || b->max_claim_slots > 65534)
     return false;
   const u32 chains = b->max_chains > 0 ? (u32)b->max_chains : 1u;
-  const u32 ns = chains <= 64 ? 1u : chains <= 128 ? 2u : 4u;
+  u32 ns = chains <= 64 ? 1u : chains <= 128 ? 2u : 4u;
   g->nq = many_claims ? 4u : 1u;
   const u32 reqs = b->max_live_requests > 0 ? (u32)b->max_live_requests : 1u;
   g->ns = ns;
@@ -1610,14 +1664,25 @@ bool rkc_lean_layout(const rkc_batch* b, rkc_lean_args* g) {
     typedef decltype(map) M;
     g->lds_bytes = M::BYTES; g->nodes_lds = M::NL; rql = M::RQL;
   };
-  if (g->nq == 4) {
-    if (ns == 1) use(LdsMap<1, 4>());
-    else if (ns == 2) use(LdsMap<2, 4>());
-    else use(LdsMap<4, 4>());
+  // Few pools: the whole batch is resident at once with every live request and 256 nodes in LDS, at
+  // most four waves per SIMD, so a pool's own latency is the time and nothing is gained by a smaller
+  // footprint (64 pools of 2,048 blocks x 1,024 events 848 -> 802 us, 3,584 pools 1,000 -> 931 us,
+  // 2,048 pools with up to 256 live claims 2,001 -> 1,885 us; 5,000 pools, not all resident at once
+  // with that footprint, 1.11 -> 1.50 ms, and at five waves per SIMD 238 -> 241 us).
+  constexpr u32 kCUs = 256, kCuWaves = 16;
+  g->few = b->n_pools <= (i32)(kCUs * kCuWaves);
+  static_assert((LdsMap<4, 4, true>::BYTES + 1279) / 1280 * 1280 * kCuWaves <= 160 * 1024, "few pools: all resident");
+  if (g->few && ns == 2) ns = g->ns = 4;  // (the key load's width does not matter there)
+  if (g->few) {
+    if (ns == 1) use(LdsMap<1, 1, true>()); else use(LdsMap<4, 1, true>());
+  } else if (g->nq == 4) {
+    if (ns == 1) use(LdsMap<1, 4, false>());
+    else if (ns == 2) use(LdsMap<2, 4, false>());
+    else use(LdsMap<4, 4, false>());
   } else {
-    if (ns == 1) use(LdsMap<1, 1>());
-    else if (ns == 2) use(LdsMap<2, 1>());
-    else use(LdsMap<4, 1>());
+    if (ns == 1) use(LdsMap<1, 1, false>());
+    else if (ns == 2) use(LdsMap<2, 1, false>());
+    else use(LdsMap<4, 1, false>());
   }
   u64 s = 0;
   g->scr_off_nodes = s;
@@ -1653,29 +1718,20 @@ unsigned rkc_lean_uniform_violations(void) {
 }
 #endif
 
-template <int NS, int NQ>
-rkc_status launch_ns(const rkc_lean_args* g, hipStream_t s) {
-  if (g->lds_bytes > 64 * 1024 &&
-      hipFuncSetAttribute((const void*)rkc_lean<NS, NQ>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                          (int)g->lds_bytes) != hipSuccess)
-    return RKC_E_HIP;
-  unsigned char* scr = (unsigned char*)g->scratch;
+rkc_status rkc_lean_launch(const rkc_lean_args* g, hipStream_t s) {
   if (g->ordered) {
+    unsigned char* scr = (unsigned char*)g->scratch;
     const unsigned tiles = (unsigned)(((u64)g->n_pools + kOrderTile - 1) / kOrderTile);
-    u32* order = (u32*)(scr + g->scr_off_order);
     hipLaunchKernelGGL(rkc_lean_order_count, dim3(tiles), dim3(kOrderTile), 0, s, g->pools, (i32)g->n_pools,
                        scr + g->scr_off_cls, (u32*)(scr + g->scr_off_tiles));
     hipLaunchKernelGGL(rkc_lean_order_scatter, dim3(tiles), dim3(kOrderTile), 0, s, (i32)g->n_pools,
-                       (const unsigned char*)(scr + g->scr_off_cls), (const u32*)(scr + g->scr_off_tiles), order);
+                       (const unsigned char*)(scr + g->scr_off_cls), (const u32*)(scr + g->scr_off_tiles),
+                       (u32*)(scr + g->scr_off_order));
     if (hipGetLastError() != hipSuccess) return RKC_E_HIP;
   }
-  hipLaunchKernelGGL((rkc_lean<NS, NQ>), dim3((unsigned)g->n_pools), dim3(64), g->lds_bytes, s, *g, g->events);
-  return hipGetLastError() == hipSuccess ? RKC_OK : RKC_E_HIP;
+  if (g->few) return rkc_lean_few_replay(g, s);
+  if (g->nq == 4) return g->ns == 1 ? replay<1, 4, false>(g, s) : g->ns == 2 ? replay<2, 4, false>(g, s) : replay<4, 4, false>(g, s);
+  return g->ns == 1 ? replay<1, 1, false>(g, s) : g->ns == 2 ? replay<2, 1, false>(g, s) : replay<4, 1, false>(g, s);
 }
 
-rkc_status rkc_lean_launch(const rkc_lean_args* g, hipStream_t s) {
-  if (g->nq == 4) return g->ns == 1 ? launch_ns<1, 4>(g, s) : g->ns == 2 ? launch_ns<2, 4>(g, s) : launch_ns<4, 4>(g, s);
-  if (g->ns == 1) return launch_ns<1, 1>(g, s);
-  if (g->ns == 2) return launch_ns<2, 1>(g, s);
-  return launch_ns<4, 1>(g, s);
-}
+#endif  // RKC_LEAN_FEW

@@ -1948,8 +1948,8 @@ uint32_t rkc_debug_uniform_violations(void) {
   unsigned v = 0;
   if (hipMemcpyFromSymbol(&v, HIP_SYMBOL(g_wave_uniform_violations), sizeof v) != hipSuccess) return ~0u;
   const unsigned w = rkc_lean_uniform_violations();
-  const unsigned x = rkc_big_uniform_violations();
-  return w == ~0u || x == ~0u ? ~0u : v + w + x;
+  const unsigned x = rkc_lean_few_uniform_violations(), y = rkc_big_uniform_violations();
+  return w == ~0u || x == ~0u || y == ~0u ? ~0u : v + w + x + y;
 }
 #endif
 

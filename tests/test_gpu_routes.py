@@ -128,3 +128,24 @@ def test_large_pool_kernel_limits(tg, usable, events):
     gen = gpu_replay(trace, flags=rkc.FLAG_GENERAL_KERNEL)
     assert not (got[1][:, 31] & ~7).any()
     compare_pools(trace, got, gen)
+
+
+# the compact kernel's layout for few pools at its largest batch and one pool past it, per claim-set
+# and key-group instantiation
+@pytest.mark.parametrize("n_pools", [4096, 4097])
+@pytest.mark.parametrize("n_chains,claims", [(3, 64), (100, 64), (3, 256), (100, 256)])
+def test_few_pools_layout(oracle_mod, n_pools, n_chains, claims):
+    import paper_2605_24259_amd as rkc
+    trace = randtrace.random_batch(77, n_pools, U_range=(4, 60), n_events=(3, 70), n_chains=n_chains, tight_every=9,
+                                   caps=(70, claims), defer=True, hard_share=0.4)
+    say(f"case few pools {n_pools} {n_chains} {claims}")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    compare_pools(trace, gpu_replay(trace), ora)
+
+
+# its nodes past the 256 in LDS, and its request list at 256 entries
+def test_few_pools_layout_past_lds(oracle_mod):
+    trace = randtrace.many_requests_batch(23, 40, n_events=(4000, 6000), n_chains=250)
+    say("case few pools past LDS")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    compare_pools(trace, gpu_replay(trace), ora)

@@ -90,18 +90,18 @@ __device__ __forceinline__ u32 ufl(u32 v) { return (u32)__builtin_amdgcn_readfir
 #endif
 __device__ __forceinline__ u32x4 ufl4(u32x4 v) { return u32x4{ufl(v.x), ufl(v.y), ufl(v.z), ufl(v.w)}; }
 __device__ __forceinline__ u32 rdl(u32 v, u32 l) { return (u32)__builtin_amdgcn_readlane((int)v, (int)l); }
-// x mod n for wave-uniform x and 1 <= n <= 16,384, on the vector unit: x / n from a double-precision
-// reciprocal refined by two Newton steps (relative error below 2^-48, so x / n is off by less than
-// 2^-16 / n), whose floor is the quotient or, when x is a multiple of n, one less; a single comparison
-// corrects that.
+// x mod n for wave-uniform x and 1 <= n <= 65,536, on the vector unit:
+// x / n from a double-precision reciprocal (v_rcp_f64: relative error about 2^-24) refined by one
+// Newton step (2^-46, so x / n is off by less than 2^-14 / n, while it is at least 1 / n below the
+// next integer unless x is n - 1 short of it).  Truncated, it is the quotient or, when x is a multiple
+// of n, one less; the smaller of the remainder and the remainder less n, unsigned, corrects that.
 __device__ __forceinline__ u32 umod(u32 x, u32 n) {
   const double dn = (double)n;
   double r = __builtin_amdgcn_rcp(dn);
   r = __builtin_fma(r, __builtin_fma(-dn, r, 1.0), r);
-  r = __builtin_fma(r, __builtin_fma(-dn, r, 1.0), r);
-  const u32 q = (u32)__builtin_floor((double)x * r);
+  const u32 q = (u32)((double)x * r);
   const u32 m = x - q * n;
-  return ufl(m >= n ? m - n : m);
+  return ufl(min(m, m - n));
 }
 __device__ __forceinline__ u32 sub0(u32 a, u32 b) { return a > b ? a - b : 0u; }
 __device__ __forceinline__ u32 wrl(u32 old, u32 v, u32 l) { return __lane_id() == l ? v : old; }
@@ -662,12 +662,9 @@ struct Big {
       F -= need;
     } else {
       u32 Ec = E;
-      u32 hlo = 0;  // candidates of chain hc start at hlo
-      if (hc >= 0) {
-        const u32 lo = max(ghc.hold, ghc.prot);
-        hlo = max(lo, h);
-        Ec -= sub0(min(ghc.n, hlo), lo);
-      }
+      // candidates of chain hc start at hlo (without one the record is all zeros and nothing is taken off)
+      const u32 lo = max(ghc.hold, ghc.prot), hlo = max(lo, h);
+      Ec -= sub0(min(ghc.n, hlo), lo);
       r.E = Ec;
       if (need > F + Ec) {
         r.ok = 0;
@@ -744,7 +741,7 @@ struct Big {
   // Refusal record of an active event that cannot be served (§3.4; §5.4 refusal record).
   __device__ __forceinline__ void refusal(u32 need, i32 hc, u32 h, u32 Hc, const G0& ghc, Out& o) {
     u32 Pr = PR;
-    if (hardm() && hc >= 0) Pr -= sub0(min(ghc.prot, h), ghc.hold);
+    if (hardm()) Pr -= sub0(min(ghc.prot, h), ghc.hold);
     const u32 req = A + Hc + need;
     o.id = -1;
     o.n16 = 0;

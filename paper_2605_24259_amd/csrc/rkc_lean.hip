@@ -104,18 +104,19 @@ __device__ __forceinline__ u32 ufl(u32 v) {
 __device__ __forceinline__ u32 ufl(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
 #endif
 __device__ __forceinline__ u32 rdl(u32 v, u32 l) { return (u32)__builtin_amdgcn_readlane((int)v, (int)l); }
-// x mod n for wave-uniform x and 1 <= n <= 1024, on the vector unit (the scalar unit is the busier
-// one): x / n from a double-precision reciprocal refined by two Newton steps (relative error below
-// 2^-48, so x / n is off by less than 2^-16 < 1 / n), whose floor is the quotient or, when x is a
-// multiple of n, one less; a single comparison corrects that.
+// x mod n for wave-uniform x and 1 <= n <= 65,536, on the vector unit (the scalar unit is the busier
+// one):
+// x / n from a double-precision reciprocal (v_rcp_f64: relative error about 2^-24) refined by one
+// Newton step (2^-46, so x / n is off by less than 2^-14 / n, while it is at least 1 / n below the
+// next integer unless x is n - 1 short of it).  Truncated, it is the quotient or, when x is a multiple
+// of n, one less; the smaller of the remainder and the remainder less n, unsigned, corrects that.
 __device__ __forceinline__ u32 umod(u32 x, u32 n) {
   const double dn = (double)n;
   double r = __builtin_amdgcn_rcp(dn);
   r = __builtin_fma(r, __builtin_fma(-dn, r, 1.0), r);
-  r = __builtin_fma(r, __builtin_fma(-dn, r, 1.0), r);
-  const u32 q = (u32)__builtin_floor((double)x * r);
+  const u32 q = (u32)((double)x * r);
   const u32 m = x - q * n;
-  return ufl(m >= n ? m - n : m);
+  return ufl(min(m, m - n));
 }
 // a - b, or 0 when b exceeds a
 __device__ __forceinline__ u32 sub0(u32 a, u32 b) { return a > b ? a - b : 0u; }
@@ -422,7 +423,11 @@ struct Lean {
   // ... and ranks victims at soft level prio + 1 (accepted soft or lowered claims still
   // materialized, and demoted claims; §3.1 soft priority, demotion to soft)
   __device__ __forceinline__ bool leveled(u32 c, u32 q) const {
-    const u32 m = lo16(qc[q]), st = m_state(m);
+    // (the barrier keeps these tests where a run's level is needed, instead of ahead of the eviction
+    // loop, where every evicting allocation would pay for them)
+    u32 m = lo16(qc[q]);
+    asm volatile("" : "+v"(m));
+    const u32 st = m_state(m);
     return on_chain(c, q) && ((st == ST_MATERIALIZED && m_eff(m) == RKC_PROT_SOFT) || st == ST_DEMOTED);
   }
   // this lane's claim of set q is a materialized hard claim (hard protection in effect)
@@ -670,12 +675,9 @@ struct Lean {
       F -= need;
     } else {
       u32 Ec = E;
-      u32 hlo = 0;  // candidates of chain hc start at hlo
-      if (hc >= 0) {
-        const u32 lo = max(ghc.hold, ghc.prot);
-        hlo = max(lo, h);
-        Ec -= sub0(min(ghc.n, hlo), lo);  // = evictable(n, lo) - evictable(n, hlo), hlo >= lo
-      }
+      // candidates of chain hc start at hlo (without one the record is all zeros and nothing is taken off)
+      const u32 lo = max(ghc.hold, ghc.prot), hlo = max(lo, h);
+      Ec -= sub0(min(ghc.n, hlo), lo);  // = evictable(n, lo) - evictable(n, hlo), hlo >= lo
       r.E = Ec;
       // (F + Ec is at most twice the usable blocks and need at most 2^24: every sum here fits 32 bits)
       if (need > F + Ec) {
@@ -781,10 +783,7 @@ struct Lean {
   struct Out;
   __device__ __forceinline__ void refusal(u32 need, i32 hc, u32 h, u32 Hc, const G0& ghc, Out& o) {
     u32 Pr = PR;
-    if (hardm() && hc >= 0) {
-      const u32 p = min(ghc.prot, h);
-      Pr -= p > ghc.hold ? p - ghc.hold : 0u;
-    }
+    if (hardm()) Pr -= sub0(min(ghc.prot, h), ghc.hold);  // (no hit chain: zeros)
     const u32 req = A + Hc + need;
     if (Pr > 0 && req <= U()) {
       o.code = RKC_OC_REFUSED_CLAIM;
@@ -1101,7 +1100,7 @@ struct Lean {
     if (bad) {
       o.code = RKC_OC_INVALID;
     } else if (nreq > 0) {
-      const u32 i = umod(w2, nreq), need = w1;
+      const u32 need = w1;
       G0 g = {0, 0, 0, 0, 0, 0, 0, 0};
       u32 relaxed = 0;
       if (ext()) relaxed = relax(t, need, -1, 0, g);
@@ -1110,7 +1109,7 @@ struct Lean {
         refusal(need, -1, 0, 0, g, o);
       } else {
         A += need;
-        o.id = (i32)lo16(rq_grow(i, need));
+        o.id = (i32)lo16(rq_grow(umod(w2, nreq), need));
         o.b = (i32)A;
         served(r, o);
         if (relaxed) { o.code = RKC_OC_RELAXED; o.n16 = min(relaxed, 65535u); }

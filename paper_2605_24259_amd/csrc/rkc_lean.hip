@@ -54,6 +54,7 @@ typedef __attribute__((address_space(1))) u32x4 glb_u32x4;
 constexpr u32 NIL = 0xFFFFu;       // 16-bit nil (positions, steps, indices are all below it)
 constexpr u32 KINF = 0xFFFFFFFFu;  // key of a chain with no candidate
 constexpr u32 NEVER = 0xFFFFFFFFu;
+constexpr u32 kLoopMax = 0x10000u;  // no walk of a touch stack is longer (counted down in its loop word)
 
 enum : u32 { ST_SUBMITTED = 0, ST_OBSERVED = 1, ST_MATERIALIZED = 2, ST_DEMOTED = 3, ST_EXPIRED = 4,
              ST_RELEASED = 5, ST_HARMED = 6, ST_REJECTED = 7 };
@@ -253,16 +254,16 @@ struct Lean {
   // the same for a wave-uniform j (address arithmetic on the vector unit)
   __device__ __forceinline__ u32x2 rq_get(u32 j) const {
     u32x2 v;
-    if (RQL >= 256u || j < RQL) v = rq[vx(j)]; else v = *gat(rqg, j - RQL);
+    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) v = rq[vx(j)]; else v = *gat(rqg, j - RQL);
     return u32x2{ufl(v.x), ufl(v.y)};
   }
   __device__ __forceinline__ void rq_put(u32 j, u32x2 v) {
-    if (RQL >= 256u || j < RQL) rq[vx(j)] = v; else *gat(rqg, j - RQL) = v;
+    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) rq[vx(j)] = v; else *gat(rqg, j - RQL) = v;
   }
   // entry j's length grows by k (a wave-uniform j); returns its first word
   __device__ __forceinline__ u32 rq_grow(u32 j, u32 k) {
     u32 x;
-    if (RQL >= 256u || j < RQL) {
+    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) {
       const u32 a = vx(j);
       const u32x2 e = rq[a];
       x = ufl(e.x);
@@ -367,15 +368,15 @@ struct Lean {
   // -- touch-stack nodes: x | t, up | down --
   __device__ __forceinline__ u32x2 nget(u32 i) {
     u32x2 v;
-    if (i < NL) v = ndl[vx(i)]; else v = *gat(ndg, i - NL);
+    if (__builtin_expect(i < NL, 1)) v = ndl[vx(i)]; else v = *gat(ndg, i - NL);
     v.x = ufl(v.x); v.y = ufl(v.y);
     return v;
   }
   __device__ __forceinline__ void nset(u32 i, u32x2 v) {
-    if (i < NL) ndl[vx(i)] = v; else *gat(ndg, i - NL) = v;
+    if (__builtin_expect(i < NL, 1)) ndl[vx(i)] = v; else *gat(ndg, i - NL) = v;
   }
   __device__ __forceinline__ void nset_y(u32 i, u32 y) {
-    if (i < NL) ((lds_u32*)(ndl + vx(i)))[1] = y; else ((__attribute__((address_space(1))) u32*)gat(ndg, i - NL))[1] = y;
+    if (__builtin_expect(i < NL, 1)) ((lds_u32*)(ndl + vx(i)))[1] = y; else ((__attribute__((address_space(1))) u32*)gat(ndg, i - NL))[1] = y;
   }
   // (the free list head and the bump pointer are read and written in the cold block where they
   // are needed: a touch that reuses a popped node needs neither)
@@ -392,7 +393,7 @@ struct Lean {
         cold[C_FNODE] = hi16(nget(i).y);
       } else {
         u32 y;
-        if (i < NL) y = ndl[i].y; else y = ndg[i - NL].y;
+        if (__builtin_expect(i < NL, 1)) y = ndl[i].y; else y = ndg[i - NL].y;
         fnode = hi16(y);
       }
     } else {
@@ -467,8 +468,8 @@ struct Lean {
         u32 b = g.sbot;
         u32x2 nb = nget(b);
         u32 up = lo16(nb.y), nxv = 0;
-        bool go = up != NIL;
-        for (u32 guard = 0; go && guard < 0x10000u; guard++) {
+        u32 left = up != NIL ? kLoopMax : 0u;
+        while (left) {
           const u32x2 nu = nget(up);
           nxv = lo16(nu.x);
           if (nxv >= g.n) {
@@ -479,9 +480,9 @@ struct Lean {
             nb = nu;
             up = lo16(nb.y);
             nxv = 0;
-            go = up != NIL;
+            left = up != NIL ? left - 1u : 0u;
           } else {
-            go = false;
+            left = 0;
           }
         }
         nset_y(b, pk(up, NIL));
@@ -501,8 +502,8 @@ struct Lean {
   // Record a touch of positions [0, x) of chain c at step t (x > 0).
   __device__ __forceinline__ void touch(G0& g, u32 x, u32 t) {
     u32 tp = g.stop, tpd = NIL, reuse = NIL;
-    bool go = tp != NIL;
-    for (u32 guard = 0; go && guard < 0x10000u; guard++) {
+    u32 left = tp != NIL ? kLoopMax : 0u;
+    while (left) {
       const u32x2 nt = nget(tp);
       tpd = hi16(nt.y);
       if (lo16(nt.x) <= x) {
@@ -514,9 +515,9 @@ struct Lean {
         }
         reuse = tp;
         tp = tpd;
-        go = tp != NIL;
+        left = tp != NIL ? left - 1u : 0u;
       } else {
-        go = false;
+        left = 0;
       }
     }
     const u32 nw = reuse != NIL ? reuse : nalloc();
@@ -693,7 +694,8 @@ struct Lean {
         u32 kf = noadm() ? KINF : FEW ? fk : ufl(cold[C_FKEY]);
         // the hit chain stops being a candidate once only hits remain
         if (hc >= 0 && ghc.n <= hlo) kk[vx(hc)] = KINF;
-        for (u32 guard = 0; K > 0; guard++) {
+        // (every pass takes at least one block off K, so the loop ends whatever it meets)
+        while (K > 0) {
           u32 kmin;
           if (NS == 4) {
             const u32x4 k4 = ((lds_u32x4*)kk)[lane];
@@ -711,7 +713,7 @@ struct Lean {
             const u32 m = min(K, ftop - flo);
             ftop -= m;
             E -= m;
-            K -= m;
+            K -= max(m, 1u);
             if (ftop == flo) fifo_pop();
             cold_fifo_out();
             kf = fk;
@@ -757,7 +759,7 @@ struct Lean {
             r.post += rs - sc;
             E -= m;
             g.n = nw;
-            K -= m;
+            K -= max(m, 1u);
             bool moved = false;
             u32 key = top_key(c, g, moved);
             // (the hit chain stops being a candidate once only hits remain; any other chain's key
@@ -771,7 +773,6 @@ struct Lean {
             set_status(0x80000000u);  // cannot happen: feasibility was checked
             K = 0;
           }
-          if (__builtin_expect(guard > 0x10000u, 0)) { set_status(0x80000000u); K = 0; }
         }
         r.unclaimed = K0 - r.resident;
       }
@@ -1070,9 +1071,9 @@ struct Lean {
 
   // (bad: the event's fields are out of range, decided for the whole tile by malformed())
   __device__ __forceinline__ void ev_prefill(u32 t, u32 w1, u32 w2, u32 w3, u32 bad, Out& o) {
-    if (bad) {
+    if (__builtin_expect(bad, 0)) {
       o.code = RKC_OC_INVALID;
-    } else if (nreq >= maxr()) {
+    } else if (__builtin_expect(nreq >= maxr(), 0)) {
       o.code = RKC_OC_INVALID;
       set_status(RKC_PS_REQUEST_TABLE);
     } else {
@@ -1097,9 +1098,9 @@ struct Lean {
   }
 
   __device__ __forceinline__ void ev_extend(u32 t, u32 w1, u32 w2, u32 bad, Out& o) {
-    if (bad) {
+    if (__builtin_expect(bad, 0)) {
       o.code = RKC_OC_INVALID;
-    } else if (nreq > 0) {
+    } else if (__builtin_expect(nreq > 0, 1)) {
       const u32 need = w1;
       G0 g = {0, 0, 0, 0, 0, 0, 0, 0};
       u32 relaxed = 0;
@@ -1118,14 +1119,14 @@ struct Lean {
   }
 
   __device__ __forceinline__ void ev_claim(u32 t, u32 w0, u32 w1, u32 w2, u32 w3, u32 bad, Out& o) {
-    if (nslot >= nslots()) {
+    if (__builtin_expect(nslot >= nslots(), 0)) {
       o.code = RKC_OC_INVALID;
       set_status(RKC_PS_SLOT_TABLE);
     } else {
       const u32 s = nslot++;
       bool ok = !bad;
       if (ok && ncl >= maxq()) { set_status(RKC_PS_CLAIM_TABLE); ok = false; }
-      if (!ok) {
+      if (__builtin_expect(!ok, 0)) {
         *gat(slot2, s) = u32x2{0u, pack_rejected(t, 0)};  // every lane, one value
         o.code = RKC_OC_INVALID;
       } else {
@@ -1185,7 +1186,7 @@ struct Lean {
   }
 
   __device__ __forceinline__ void ev_finish(u32 t, u32 w1, Out& o) {
-    if (nreq > 0) {
+    if (__builtin_expect(nreq > 0, 1)) {
       const u32 i = umod(w1, nreq);
       const u32x2 e = rq_get(i);
       const u32 rid = lo16(e.x), c = hi16(e.x), R = lo16(e.y), len = hi16(e.y);

@@ -124,19 +124,34 @@ __device__ __forceinline__ u32 sub0(u32 a, u32 b) { return a > b ? a - b : 0u; }
 // lane l of `old` replaced by the uniform value v
 __device__ __forceinline__ u32 wrl(u32 old, u32 v, u32 l) { return __lane_id() == l ? v : old; }
 __device__ __forceinline__ u64 ballot(bool p) { return __ballot(p); }
-// A wave-uniform index moved to a vector register, so that the address arithmetic of an LDS or
-// global access at that index runs on the vector unit: the scalar unit is the busier one, and a
-// global address from a scalar index takes three scalar instructions (64-bit shift and add).
+// A wave-uniform value moved to a vector register, so that the arithmetic on it runs on the vector unit:
+// the scalar unit is the busier one.
 __device__ __forceinline__ u32 vx(u32 i) {
   u32 r;
   asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(ufl(i)));
   return r;
 }
-// &base[i] for a wave-uniform i, the byte offset formed on the vector unit (a 32-bit offset to a
-// scalar base, which the global instructions take as such)
+// The byte offset of entry i (wave-uniform) of an array of T, formed in one vector instruction.
+template <class T>
+__device__ __forceinline__ u32 vofs(u32 i) {
+  constexpr int sh = sizeof(T) == 4 ? 2 : sizeof(T) == 8 ? 3 : 4;
+  static_assert(sizeof(T) == 1u << sh, "entries of 4, 8 or 16 bytes");
+  u32 r;
+  asm("v_lshlrev_b32_e64 %0, %1, %2" : "=v"(r) : "n"(sh), "s"(ufl(i)));
+  return r;
+}
+// &base[i] of a global array for a wave-uniform i (a 32-bit offset to a scalar base, which the global
+// instructions take as such).
 template <class T>
 __device__ __forceinline__ T* gat(T* base, u32 i) {
-  return (T*)((__attribute__((address_space(1))) char*)base + (u64)(vx(i) * (u32)sizeof(T)));
+  return (T*)((__attribute__((address_space(1))) char*)base + (u64)vofs<T>(i));
+}
+// Entry i (wave-uniform) of the array at byte `at` of the workgroup's LDS.  The kernel has no static LDS,
+// so its dynamic LDS starts at address 0 and `at` folds into the access: a pointer formed from the
+// LDS array's name takes a second vector instruction per access to add its address, 0.
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lat(u32 at, u32 i) {
+  return (__attribute__((address_space(3))) T*)(vofs<T>(i) + at);
 }
 
 // every source lane exists for the permutes used here, so the moved value never needs an old
@@ -206,6 +221,7 @@ struct LdsMap {
 // relaxes, whose loop carries the deferral ring and the runtime relaxation.
 template <int NS, int NQ, int MODE, bool EXT, bool FEW>
 struct Lean {
+  typedef LdsMap<NS, NQ, FEW> M;
   static constexpr u32 KC = 64u * NS;  // key slots (chains padded to whole lanes)
   // descriptor: the rarely used limits one per lane of `cst`
   static constexpr u32 mode = MODE;
@@ -254,21 +270,21 @@ struct Lean {
   // the same for a wave-uniform j (address arithmetic on the vector unit)
   __device__ __forceinline__ u32x2 rq_get(u32 j) const {
     u32x2 v;
-    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) v = rq[vx(j)]; else v = *gat(rqg, j - RQL);
+    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) v = *lat<u32x2>(M::RQ, j); else v = *gat(rqg, j - RQL);
     return u32x2{ufl(v.x), ufl(v.y)};
   }
   __device__ __forceinline__ void rq_put(u32 j, u32x2 v) {
-    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) rq[vx(j)] = v; else *gat(rqg, j - RQL) = v;
+    if (RQL >= 256u || __builtin_expect(j < RQL, 1)) *lat<u32x2>(M::RQ, j) = v; else *gat(rqg, j - RQL) = v;
   }
   // entry j's length grows by k (a wave-uniform j); returns its first word
   __device__ __forceinline__ u32 rq_grow(u32 j, u32 k) {
     u32 x;
     if (RQL >= 256u || __builtin_expect(j < RQL, 1)) {
-      const u32 a = vx(j);
-      const u32x2 e = rq[a];
+      lds_u32x2* a = lat<u32x2>(M::RQ, j);
+      const u32x2 e = *a;
       x = ufl(e.x);
       const u32 y = ufl(e.y);
-      rq[a] = u32x2{x, pk(lo16(y), hi16(y) + k)};
+      *a = u32x2{x, pk(lo16(y), hi16(y) + k)};
     } else {
       glb_u32x2* a = gat(rqg, j - RQL);
       const u32x2 e = *a;
@@ -351,7 +367,7 @@ struct Lean {
 
   // -- chain records --
   __device__ __forceinline__ G0 rd0(u32 c) {
-    const u32x4 v = ch[vx(c)];
+    const u32x4 v = *lat<u32x4>(M::CH, c);
     const u32 a = ufl(v.x), b = ufl(v.y), d = ufl(v.z), e = ufl(v.w);
     // (only hard-protection pools ever protect positions: elsewhere the field is 0, and saying so
     // here lets the compiler drop the protection terms from those pools' loops)
@@ -360,7 +376,7 @@ struct Lean {
   __device__ __forceinline__ void wr0(u32 c, const G0& g) {
     u32x4 v;
     v.x = pk(g.n, g.hold); v.y = pk(g.prot, g.bt); v.z = pk(g.nx, g.covA); v.w = pk(g.stop, g.sbot);
-    ch[vx(c)] = v;
+    *lat<u32x4>(M::CH, c) = v;
   }
   __device__ __forceinline__ u32 chain_n(u32 c) { return lo16(((lds_u32*)(ch + c))[0]); }
   __device__ __forceinline__ u32 chain_hold(u32 c) { return hi16(((lds_u32*)(ch + c))[0]); }
@@ -368,15 +384,15 @@ struct Lean {
   // -- touch-stack nodes: x | t, up | down --
   __device__ __forceinline__ u32x2 nget(u32 i) {
     u32x2 v;
-    if (__builtin_expect(i < NL, 1)) v = ndl[vx(i)]; else v = *gat(ndg, i - NL);
+    if (__builtin_expect(i < NL, 1)) v = *lat<u32x2>(M::ND, i); else v = *gat(ndg, i - NL);
     v.x = ufl(v.x); v.y = ufl(v.y);
     return v;
   }
   __device__ __forceinline__ void nset(u32 i, u32x2 v) {
-    if (__builtin_expect(i < NL, 1)) ndl[vx(i)] = v; else *gat(ndg, i - NL) = v;
+    if (__builtin_expect(i < NL, 1)) *lat<u32x2>(M::ND, i) = v; else *gat(ndg, i - NL) = v;
   }
   __device__ __forceinline__ void nset_y(u32 i, u32 y) {
-    if (__builtin_expect(i < NL, 1)) ((lds_u32*)(ndl + vx(i)))[1] = y; else ((__attribute__((address_space(1))) u32*)gat(ndg, i - NL))[1] = y;
+    if (__builtin_expect(i < NL, 1)) ((lds_u32*)lat<u32x2>(M::ND, i))[1] = y; else ((__attribute__((address_space(1))) u32*)gat(ndg, i - NL))[1] = y;
   }
   // (the free list head and the bump pointer are read and written in the cold block where they
   // are needed: a touch that reuses a popped node needs neither)
@@ -393,7 +409,7 @@ struct Lean {
         cold[C_FNODE] = hi16(nget(i).y);
       } else {
         u32 y;
-        if (__builtin_expect(i < NL, 1)) y = ndl[i].y; else y = ndg[i - NL].y;
+        if (__builtin_expect(i < NL, 1)) y = lat<u32x2>(M::ND, i)->y; else y = gat(ndg, i - NL)->y;
         fnode = hi16(y);
       }
     } else {
@@ -541,7 +557,8 @@ struct Lean {
     g.n = nn; g.hold = hh; g.prot = pp;
     if (x) touch(g, x, t);
     bool moved = false;
-    kk[vx(c)] = top_key(c, g, moved);
+    const u32 key = top_key(c, g, moved);
+    *lat<u32>(M::KEYS, c) = key;
     wr0(c, g);
   }
 
@@ -693,7 +710,7 @@ struct Lean {
         // the front private run's key (the rest of the FIFO state is read when a run is taken)
         u32 kf = noadm() ? KINF : FEW ? fk : ufl(cold[C_FKEY]);
         // the hit chain stops being a candidate once only hits remain
-        if (hc >= 0 && ghc.n <= hlo) kk[vx(hc)] = KINF;
+        if (hc >= 0 && ghc.n <= hlo) *lat<u32>(M::KEYS, (u32)hc) = KINF;
         // (every pass takes at least one block off K, so the loop ends whatever it meets)
         while (K > 0) {
           u32 kmin;
@@ -765,10 +782,10 @@ struct Lean {
             // (the hit chain stops being a candidate once only hits remain; any other chain's key
             // is already KINF when nw <= lo)
             if (nw <= lo) key = KINF;
-            kk[vx(c)] = key;
+            *lat<u32>(M::KEYS, c) = key;
             // (only n changed unless the stack bottom advanced)
             if (moved) wr0(c, g);
-            else ((lds_u32*)(ch + vx(c)))[0] = pk(g.n, g.hold);
+            else *(lds_u32*)lat<u32x4>(M::CH, c) = pk(g.n, g.hold);
           } else {
             set_status(0x80000000u);  // cannot happen: feasibility was checked
             K = 0;

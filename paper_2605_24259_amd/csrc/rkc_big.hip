@@ -49,6 +49,7 @@ typedef __attribute__((address_space(1))) u32x4 glb_u32x4;
 constexpr u32 NIL = 0xFFFFFFFFu;
 constexpr u32 KINF = 0xFFFFFFFFu;  // key of a chain with no candidate
 constexpr u32 NEVER = 0xFFFFFFFFu;
+constexpr u32 kLoopMax = 0x20000u;  // no walk of a touch stack is longer (counted down in its loop word)
 
 enum : u32 { ST_OBSERVED = 1, ST_MATERIALIZED = 2, ST_DEMOTED = 3, ST_EXPIRED = 4, ST_RELEASED = 5, ST_HARMED = 6,
              ST_REJECTED = 7 };
@@ -114,14 +115,17 @@ __device__ __forceinline__ u32 dpp(u32 v) {
 struct OpMax { __device__ static u32 f(u32 a, u32 b) { return a > b ? a : b; } };
 struct OpMin { __device__ static u32 f(u32 a, u32 b) { return a < b ? a : b; } };
 struct OpAdd { __device__ static u32 f(u32 a, u32 b) { return a + b; } };
-// Row-level butterflies (quad perms, half-row and row mirrors), then the four row results.
+// Row-level butterflies (quad perms, half-row and row mirrors), then two row broadcasts that leave the
+// result in lane 63 (the rows they have no source for are not used).
 template <class Op>
 __device__ __forceinline__ u32 wreduce(u32 v) {
   v = Op::f(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
   v = Op::f(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
   v = Op::f(v, dpp<0x141>(v));  // row_half_mirror
   v = Op::f(v, dpp<0x140>(v));  // row_mirror
-  return Op::f(Op::f(rdl(v, 0), rdl(v, 16)), Op::f(rdl(v, 32), rdl(v, 48)));
+  v = Op::f(v, dpp<0x142>(v));  // row_bcast:15
+  v = Op::f(v, dpp<0x143>(v));  // row_bcast:31
+  return rdl(v, 63);
 }
 __device__ __forceinline__ u32 wmax(u32 v) { return wreduce<OpMax>(v); }
 __device__ __forceinline__ u32 wmin(u32 v) { return wreduce<OpMin>(v); }
@@ -329,25 +333,25 @@ struct Big {
   // -- touch-stack nodes --
   __device__ __forceinline__ u32x4 nget(u32 i) {
     u32x4 v;
-    if (i < nl) v = ndl[i]; else v = ndg[i - nl];
+    if (__builtin_expect(i < nl, 1)) v = ndl[i]; else v = ndg[i - nl];
     return ufl4(v);
   }
   __device__ __forceinline__ void nset(u32 i, u32x4 v) {
-    if (i < nl) ndl[i] = v; else ndg[i - nl] = v;
+    if (__builtin_expect(i < nl, 1)) ndl[i] = v; else ndg[i - nl] = v;
   }
   __device__ __forceinline__ void nset_links(u32 i, u32 up, u32 down) {
-    if (i < nl) ((lds_u32x2*)(ndl + i))[1] = u32x2{up, down};
+    if (__builtin_expect(i < nl, 1)) ((lds_u32x2*)(ndl + i))[1] = u32x2{up, down};
     else ((glb_u32x2*)(ndg + (i - nl)))[1] = u32x2{up, down};
   }
   __device__ __forceinline__ void nset_t(u32 i, u32 t) {
-    if (i < nl) ((lds_u32*)(ndl + i))[1] = t; else ((glb_u32*)(ndg + (i - nl)))[1] = t;
+    if (__builtin_expect(i < nl, 1)) ((lds_u32*)(ndl + i))[1] = t; else ((glb_u32*)(ndg + (i - nl)))[1] = t;
   }
   // free list (its head stays in a vector register: the next head's load is not waited for here)
   u32 fnode, bump;
   __device__ __forceinline__ u32 nalloc() {
     u32 i = ufl(fnode);
     if (i != NIL) {
-      if (i < nl) fnode = ndl[i].w; else fnode = ndg[i - nl].w;
+      if (__builtin_expect(i < nl, 1)) fnode = ndl[i].w; else fnode = ndg[i - nl].w;
     } else if (bump < ncap()) {
       i = bump++;
     } else {
@@ -466,8 +470,8 @@ struct Big {
         u32 b = g.sbot;
         u32x4 nb = nget(b);
         u32 up = nb.z, nxv = 0;
-        bool go = up != NIL;
-        for (u32 guard = 0; go && guard < 0x20000u; guard++) {
+        u32 left = up != NIL ? kLoopMax : 0u;
+        while (left) {
           const u32x4 nu = nget(up);
           nxv = nu.x;
           if (nxv >= g.n) {
@@ -476,9 +480,9 @@ struct Big {
             nb = nu;
             up = nb.z;
             nxv = 0;
-            go = up != NIL;
+            left = up != NIL ? left - 1u : 0u;
           } else {
-            go = false;
+            left = 0;
           }
         }
         nset_links(b, up, NIL);
@@ -495,8 +499,8 @@ struct Big {
   // Record a touch of positions [0, x) of chain c at step t (x > 0).
   __device__ __forceinline__ void touch(G0& g, u32 x, u32 t) {
     u32 tp = g.stop, tpd = NIL, reuse = NIL, same = 0;
-    bool go = tp != NIL;
-    for (u32 guard = 0; go && guard < 0x20000u; guard++) {
+    u32 left = tp != NIL ? kLoopMax : 0u;
+    while (left) {
       const u32x4 nt = nget(tp);
       tpd = nt.w;
       if (nt.x < x) {
@@ -504,10 +508,10 @@ struct Big {
         if (reuse != NIL) nfree(reuse);
         reuse = tp;
         tp = tpd;
-        go = tp != NIL;
+        left = tp != NIL ? left - 1u : 0u;
       } else {
         same = nt.x == x;
-        go = false;
+        left = 0;
       }
     }
     u32 st = tp, sb = g.sbot, bt = g.bt, nx = g.nx;
@@ -674,14 +678,15 @@ struct Big {
         const u32 K0 = K;
         vic += K;
         if (hc >= 0 && ghc.n <= hlo) kk[(u32)hc] = KINF;
-        for (u32 guard = 0; K > 0; guard++) {
+        // (every pass takes at least one block off K, so the loop ends whatever it meets)
+        while (K > 0) {
           const u32x4 k4 = ((lds_u32x4*)kk)[lane];
           const u32 m1 = wmin(min(min(k4.x, k4.y), min(k4.z, k4.w)));
           if (!noadm() && fkey < m1) {
             // the oldest finished request's private run (level 0)
             const u32 m = min(K, ftop - flo);
             E -= m;
-            K -= m;
+            K -= max(m, 1u);
             ftop -= m;
             if (ftop == flo) fifo_pop();
           } else if (m1 != KINF) {
@@ -714,7 +719,7 @@ struct Big {
             }
             E -= m;
             g.n = nw;
-            K -= m;
+            K -= max(m, 1u);
             bool moved = false;
             u32 key = top_key(c, g, moved);
             if (nw <= lo) key = KINF;
@@ -725,7 +730,6 @@ struct Big {
             set_status(0x80000000u);  // cannot happen: feasibility was checked
             K = 0;
           }
-          if (__builtin_expect(guard > 0x200000u, 0)) { set_status(0x80000000u); K = 0; }
         }
         r.unclaimed = K0 - r.resident;
       }
@@ -968,9 +972,9 @@ struct Big {
   }
 
   __device__ __forceinline__ void ev_prefill(u32 t, u32 w1, u32 w2, u32 w3, u32 bad, Out& o) {
-    if (bad) {
+    if (__builtin_expect(bad, 0)) {
       o.code = RKC_OC_INVALID;
-    } else if (nreq >= maxr()) {
+    } else if (__builtin_expect(nreq >= maxr(), 0)) {
       o.code = RKC_OC_INVALID;
       set_status(RKC_PS_REQUEST_TABLE);
     } else {
@@ -992,9 +996,9 @@ struct Big {
   }
 
   __device__ __forceinline__ void ev_extend(u32 t, u32 w1, u32 w2, u32 bad, Out& o) {
-    if (bad) {
+    if (__builtin_expect(bad, 0)) {
       o.code = RKC_OC_INVALID;
-    } else if (nreq > 0) {
+    } else if (__builtin_expect(nreq > 0, 1)) {
       const u32 need = w1, at = ring(umod(w2, nreq));
       const u32x2 e = rq[at];  // (in flight over the allocation)
       G0 g = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -1015,14 +1019,14 @@ struct Big {
   }
 
   __device__ __forceinline__ void ev_claim(u32 t, u32 w0, u32 w1, u32 w2, u32 w3, u32 bad, Out& o) {
-    if (nslot >= nslots()) {
+    if (__builtin_expect(nslot >= nslots(), 0)) {
       o.code = RKC_OC_INVALID;
       set_status(RKC_PS_SLOT_TABLE);
     } else {
       const u32 s = nslot++;
       bool ok = !bad;
       if (ok && ncl >= maxq()) { set_status(RKC_PS_CLAIM_TABLE); ok = false; }
-      if (!ok) {
+      if (__builtin_expect(!ok, 0)) {
         slot2[s] = u32x2{0u, pack_rejected(t, 0)};  // every lane, one value
         o.code = RKC_OC_INVALID;
       } else {
@@ -1225,7 +1229,7 @@ struct Big {
   __device__ __forceinline__ void step(u32 t, u32 w0, u32 w1, u32 w2, u32 w3, u32 bad, Out& o) {
     const u32 type = w0 & 15u;
     o = Out{RKC_OC_NOOP, 0, 0, -1, 0, 0};
-    if (!shadm() && t >= nexp) {
+    if (!shadm() && __builtin_expect(t >= nexp, 0)) {
       u32 expired;
       expire(t, o.flags, expired);
       o.n16 = min(expired, 65535u);
@@ -1237,7 +1241,7 @@ struct Big {
     else if (type == RKC_EV_RELEASE || type == RKC_EV_DEMOTE) ev_lifecycle(t, type, w1, o);
     else if (ext() && type == RKC_EV_RETRY) ev_retry(t, o);
     else if ((type & ~1u) != RKC_EV_NOP) o.code = RKC_OC_INVALID;  // NOP, or RETRY with no ring
-    if (sweep_due) {
+    if (__builtin_expect(sweep_due, 0)) {
       sweep_due = 0;
       o.flags |= sweep(t);
     }

@@ -154,8 +154,9 @@ __device__ __forceinline__ __attribute__((address_space(3))) T* lat(u32 at, u32 
   return (__attribute__((address_space(3))) T*)(vofs<T>(i) + at);
 }
 
-// every source lane exists for the permutes used here, so the moved value never needs an old
-// value and the move folds into the consuming min / max / add
+// every source lane exists for the permutes used here (but for the row broadcasts' first rows, whose
+// results are not used), so the moved value never needs an old value and the move folds into the
+// consuming min / max / add
 template <int CTRL>
 __device__ __forceinline__ u32 dpp(u32 v) {
   return (u32)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
@@ -163,18 +164,25 @@ __device__ __forceinline__ u32 dpp(u32 v) {
 struct OpMax { __device__ static u32 f(u32 a, u32 b) { return a > b ? a : b; } };
 struct OpMin { __device__ static u32 f(u32 a, u32 b) { return a < b ? a : b; } };
 struct OpAdd { __device__ static u32 f(u32 a, u32 b) { return a + b; } };
-// Row-level butterflies (quad perms, half-row and row mirrors), then the four row results.
-template <class Op>
+// Row-level butterflies (quad perms, half-row and row mirrors), then the four row results: by scalar
+// reads of each row, or (CHAIN) by two row broadcasts that leave the result in lane 63.  The chain is
+// fewer instructions but two more dependent steps: it wins where a pool's latency or the claim sets'
+// many reductions are the time (64 zipf pools 752 -> 728 us, 4,096 pools of 80 blocks 209.6 -> 204.5,
+// nested 4,035 -> 3,945) and loses on one claim set at 25 pools a CU (zipf 10,010 -> 10,050 us,
+// zipf_offload 3,839 -> 3,913).
+template <class Op, bool CHAIN>
 __device__ __forceinline__ u32 wreduce(u32 v) {
   v = Op::f(v, dpp<0xB1>(v));   // quad_perm [1,0,3,2]
   v = Op::f(v, dpp<0x4E>(v));   // quad_perm [2,3,0,1]
   v = Op::f(v, dpp<0x141>(v));  // row_half_mirror
   v = Op::f(v, dpp<0x140>(v));  // row_mirror
+  if (CHAIN) {
+    v = Op::f(v, dpp<0x142>(v));  // row_bcast:15 (rows 1 and 3 hold rows 0-1 and 2-3)
+    v = Op::f(v, dpp<0x143>(v));  // row_bcast:31 (row 3 holds all)
+    return rdl(v, 63);
+  }
   return Op::f(Op::f(rdl(v, 0), rdl(v, 16)), Op::f(rdl(v, 32), rdl(v, 48)));
 }
-__device__ __forceinline__ u32 wmax(u32 v) { return wreduce<OpMax>(v); }
-__device__ __forceinline__ u32 wmin(u32 v) { return wreduce<OpMin>(v); }
-__device__ __forceinline__ u32 wsum(u32 v) { return wreduce<OpAdd>(v); }
 // lane l receives lane l + 1's value (lane 63 keeps its own)
 __device__ __forceinline__ u32 shift_down(u32 v) {
   return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
@@ -222,6 +230,10 @@ struct LdsMap {
 template <int NS, int NQ, int MODE, bool EXT, bool FEW>
 struct Lean {
   typedef LdsMap<NS, NQ, FEW> M;
+  static constexpr bool CHAIN = FEW || NQ > 1;  // form of the wave reductions
+  __device__ __forceinline__ static u32 wmax(u32 v) { return wreduce<OpMax, CHAIN>(v); }
+  __device__ __forceinline__ static u32 wmin(u32 v) { return wreduce<OpMin, CHAIN>(v); }
+  __device__ __forceinline__ static u32 wsum(u32 v) { return wreduce<OpAdd, CHAIN>(v); }
   static constexpr u32 KC = 64u * NS;  // key slots (chains padded to whole lanes)
   // descriptor: the rarely used limits one per lane of `cst`
   static constexpr u32 mode = MODE;
@@ -1464,9 +1476,9 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
     const u32 oc = o0 & 255u;
     __hip_atomic_fetch_add(P.hist + (P.lane < cnt ? oc : 15u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     const bool srv = P.lane < cnt && (oc <= RKC_OC_EVICT_RESIDENT || (LP::ext() && oc == RKC_OC_RELAXED));
-    P.tadd(TW_RESIDENT, wsum(srv ? o2 : 0u));
+    P.tadd(TW_RESIDENT, LP::wsum(srv ? o2 : 0u));
     const u32 ty = e0 & 15u;
-    P.tadd(TW_HITS, wsum(srv && (ty == RKC_EV_PREFILL || (LP::ext() && ty == RKC_EV_RETRY)) ? o3 : 0u));
+    P.tadd(TW_HITS, LP::wsum(srv && (ty == RKC_EV_PREFILL || (LP::ext() && ty == RKC_EV_RETRY)) ? o3 : 0u));
   }
 
   const u32 nslot_used = P.nslot;

@@ -105,6 +105,19 @@ __device__ __forceinline__ u32 umod(u32 x, u32 n) {
   return ufl(min(m, m - n));
 }
 __device__ __forceinline__ u32 sub0(u32 a, u32 b) { return a > b ? a - b : 0u; }
+// The byte offset of entry i (wave-uniform) of an array of 2^SH-byte entries, in one vector instruction.
+template <int SH>
+__device__ __forceinline__ u32 vofs(u32 i) {
+  u32 r;
+  asm("v_lshlrev_b32_e64 %0, %1, %2" : "=v"(r) : "n"(SH), "s"(ufl(i)));
+  return r;
+}
+// Entry i (wave-uniform) of the array of 2^SH-byte entries at byte `at` of the workgroup's LDS (the kernel
+// has no static LDS, so its dynamic LDS starts at address 0).
+template <class T, int SH>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lat(u32 at, u32 i) {
+  return (__attribute__((address_space(3))) T*)(vofs<SH>(i) + at);
+}
 __device__ __forceinline__ u32 wrl(u32 old, u32 v, u32 l) { return __lane_id() == l ? v : old; }
 __device__ __forceinline__ u64 ballot(bool p) { return __ballot(p); }
 
@@ -238,12 +251,14 @@ struct Big {
 
   // -- chain records --
   __device__ __forceinline__ G0 rd0(u32 c) {
-    const u32x4 a = ch[2 * c], b = ch[2 * c + 1];
+    const lds_u32x4* r = lat<u32x4, 5>(L_CH, c);
+    const u32x4 a = r[0], b = r[1];
     return G0{ufl(a.x), ufl(a.y), hardm() ? ufl(a.z) : 0u, ufl(a.w), ufl(b.x), ufl(b.y), ufl(b.z), ufl(b.w)};
   }
   __device__ __forceinline__ void wr0(u32 c, const G0& g) {
-    ch[2 * c] = u32x4{g.n, g.hold, g.prot, g.bt};
-    ch[2 * c + 1] = u32x4{g.nx, g.covA, g.stop, g.sbot};
+    lds_u32x4* r = lat<u32x4, 5>(L_CH, c);
+    r[0] = u32x4{g.n, g.hold, g.prot, g.bt};
+    r[1] = u32x4{g.nx, g.covA, g.stop, g.sbot};
   }
   __device__ __forceinline__ u32 chain_n(u32 c) { return ((lds_u32*)(ch + 2 * c))[0]; }
   __device__ __forceinline__ u32 chain_hold(u32 c) { return ((lds_u32*)(ch + 2 * c))[1]; }
@@ -547,7 +562,8 @@ struct Big {
     g.n = nn; g.hold = hh; g.prot = pp;
     if (x) touch(g, x, t);
     bool moved = false;
-    kk[c] = top_key(c, g, moved);
+    const u32 key = top_key(c, g, moved);
+    *lat<u32, 2>(L_KEYS, c) = key;
     wr0(c, g);
   }
 
@@ -677,7 +693,7 @@ struct Big {
         F = 0;
         const u32 K0 = K;
         vic += K;
-        if (hc >= 0 && ghc.n <= hlo) kk[(u32)hc] = KINF;
+        if (hc >= 0 && ghc.n <= hlo) *lat<u32, 2>(L_KEYS, (u32)hc) = KINF;
         // (every pass takes at least one block off K, so the loop ends whatever it meets)
         while (K > 0) {
           const u32x4 k4 = ((lds_u32x4*)kk)[lane];
@@ -723,9 +739,9 @@ struct Big {
             bool moved = false;
             u32 key = top_key(c, g, moved);
             if (nw <= lo) key = KINF;
-            kk[c] = key;
+            *lat<u32, 2>(L_KEYS, c) = key;
             if (moved) wr0(c, g);
-            else ((lds_u32*)(ch + 2 * c))[0] = g.n;
+            else *lat<u32, 5>(L_CH, c) = g.n;
           } else {
             set_status(0x80000000u);  // cannot happen: feasibility was checked
             K = 0;
@@ -904,7 +920,7 @@ struct Big {
     G0 g = {0, 0, 0, 0, 0, 0, 0, 0};
     if (P > 0) {
       hc = (i32)cc;
-      hk = hcnt[cc];
+      hk = *lat<u32, 2>(L_HCNT, cc);
       g = rd0(cc);
       h = min(P, g.n);
       Hc = sub0(h, g.hold);
@@ -944,7 +960,7 @@ struct Big {
         R = noadm() ? h : P;
         const u32 nn = (!noadm() && P > g2.n) ? P : g2.n;
         // (the chain's hold is the largest R of its live requests; hcnt counts those holding it)
-        if (R > 0 && R >= g2.hold) hcnt[cc] = R > g2.hold ? 1u : hk + 1u;
+        if (R > 0 && R >= g2.hold) *lat<u32, 2>(L_HCNT, cc) = R > g2.hold ? 1u : hk + 1u;
         commit(cc, g2, nn, max(g2.hold, R), g2.prot, R, t);
       }
       const u32x2 e = rq_pack(rid, hc >= 0 ? cc : 0u, R, S);
@@ -953,7 +969,7 @@ struct Big {
         dq_pop(dh, dl);
         tadd(TW_RETRY_SERVED, 1);
       } else {
-        rq[ring(nreq)] = e;
+        *lat<u32x2, 3>(L_RQ, ring(nreq)) = e;
       }
       nreq++;
       o.id = (i32)rid;
@@ -1000,7 +1016,8 @@ struct Big {
       o.code = RKC_OC_INVALID;
     } else if (__builtin_expect(nreq > 0, 1)) {
       const u32 need = w1, at = ring(umod(w2, nreq));
-      const u32x2 e = rq[at];  // (in flight over the allocation)
+      lds_u32x2* ep = lat<u32x2, 3>(L_RQ, at);
+      const u32x2 e = *ep;  // (in flight over the allocation)
       G0 g = {0, 0, 0, 0, 0, 0, 0, 0};
       u32 relaxed = 0;
       if (ext()) relaxed = relax(t, need, -1, 0, g);
@@ -1009,7 +1026,7 @@ struct Big {
         refusal(need, -1, 0, 0, g, o);
       } else {
         A += need;
-        ((lds_u32*)(rq + at))[1] = e.y + need;  // (a length stays below 2^20: it never exceeds U)
+        ((lds_u32*)ep)[1] = e.y + need;  // (a length stays below 2^20: it never exceeds U)
         o.id = (i32)ufl(rq_id(e));
         o.b = (i32)A;
         served(r, o);
@@ -1080,13 +1097,13 @@ struct Big {
   __device__ __forceinline__ void ev_finish(u32 t, u32 w1, Out& o) {
     if (nreq > 0) {
       const u32 i = umod(w1, nreq);
-      const u32x2 e0 = rq[ring(i)];
+      const u32x2 e0 = *lat<u32x2, 3>(L_RQ, ring(i));
       const u32x2 e = u32x2{ufl(e0.x), ufl(e0.y)};
       const u32 rid = rq_id(e), c = rq_c(e), R = rq_R(e), len = rq_len(e);
       G0 g;
       u32 hk = 0;
       if (R > 0) {
-        hk = hcnt[c];
+        hk = *lat<u32, 2>(L_HCNT, c);
         g = rd0(c);
       }
       rq_remove(i);
@@ -1097,11 +1114,11 @@ struct Big {
         if (R == hn) {
           hk = ufl(hk);
           if (hk > 1) {
-            hcnt[c] = hk - 1;
+            *lat<u32, 2>(L_HCNT, c) = hk - 1;
           } else {
             u32 cnt;
             hn = rq_hold(c, cnt);
-            hcnt[c] = cnt;
+            *lat<u32, 2>(L_HCNT, c) = cnt;
           }
         }
         turned = sub0(R, hn);

@@ -22,8 +22,8 @@
 // front sit in registers, loads are issued before they are needed (free-list head, FIFO's next run,
 // hold count), and touching the prefix that was touched last only rewrites a step (4.17 -> 3.52 ms
 // and 60.9 -> 54.5 ms on the batches below).
-// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 135.3 -> 54.5 ms,
-// 512 pools of 65,536 blocks x 4,096 events 7.66 -> 3.52 ms (under 1 us an event either way).
+// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 135.3 -> 50.6 ms,
+// 512 pools of 65,536 blocks x 4,096 events 7.66 -> 3.38 ms (about 0.8 us an event either way).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -158,7 +158,6 @@ struct AllocRes { u32 ok, E, resident, post, unclaimed, hit; };
 constexpr u32 kChains = 256, kClaimsLds = 256;
 constexpr u32 L_COLD = 0, L_HIST = 64, L_KEYS = 128, L_HCNT = L_KEYS + 4 * kChains, L_MARK = L_HCNT + 4 * kChains,
               L_CH = L_MARK + 64, L_CL = L_CH + 32 * kChains, L_CX = L_CL + 16 * kClaimsLds, L_RQ = L_CX + 8 * kClaimsLds;
-constexpr u32 kShift = 8;  // 64-entry chunks a ring shift keeps in flight
 
 // ---- one pool ---------------------------------------------------------------------------------
 // MODE: the pool policy; EXT: a hard-protection pool that defers or relaxes.
@@ -272,40 +271,49 @@ struct Big {
   __device__ __forceinline__ static u32 rq_R(u32x2 e) { return e.x & 0xFFFFFu; }
   __device__ __forceinline__ static u32 rq_len(u32x2 e) { return e.y & 0xFFFFFu; }
   __device__ __forceinline__ u32 ring(u32 j) const { return (rhead + j) & rmask; }
-  // Entries [i, n) move by one place: up = false closes a gap below them (they move to i - 1 ...),
-  // up = true opens one at i.  Each round loads kShift chunks before it stores any, running away
-  // from the destination, so no store lands on an entry a later round still loads.
-  __device__ __forceinline__ void rq_down(u32 i, u32 n) {
-    for (u32 base = i; base < n; base += 64 * kShift) {
-      u32x2 v[kShift];
+  // Entries [lo, hi), at most 64 KU of them, move by one place (D = -1 or 1).  All are loaded before any is
+  // stored.  Where neither side wraps around the ring, one address with constant offsets serves every
+  // access; entries past hi are loaded with the rest and not stored.
+  template <int KU, int D>
+  __device__ __forceinline__ void rq_move(u32 lo, u32 hi) {
+    const u32 p = ring(lo);
+    u32x2 v[KU];
+    if (__builtin_expect(p >= 1u && p + 64u * KU <= rmask, 1)) {
+      lds_u32x2* q = rq + p + lane;
 #pragma unroll
-      for (u32 u = 0; u < kShift; u++)
-        if (base + 64 * u < n) v[u] = rq[ring(base + 64 * u + lane)];
+      for (int u = 0; u < KU; u++) v[u] = q[64 * u];
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (u32 u = 0; u < kShift; u++) {
-        const u32 j = base + 64 * u + lane;
-        if (base + 64 * u < n && j < n) rq[ring(j - 1)] = v[u];
-      }
+      for (int u = 0; u < KU; u++)
+        if (lo + 64u * u + lane < hi) q[64 * u + D] = v[u];
+    } else {
+#pragma unroll
+      for (int u = 0; u < KU; u++) v[u] = rq[ring(lo + 64u * u + lane)];
       __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < KU; u++)
+        if (lo + 64u * u + lane < hi) rq[ring(lo + 64u * u + lane + D)] = v[u];
     }
+    __builtin_amdgcn_wave_barrier();
+  }
+  // Entries [i, n) move down one place (closing a gap below them) or up one place (opening one at i), in
+  // rounds that run away from the destination, so that no store lands on an entry a later round loads:
+  // rounds of 512 entries, the last 128 in rounds of their own (a round costs its chunks, full or not).
+  __device__ __forceinline__ void rq_down(u32 i, u32 n) {
+    while (n > i + 128) {
+      const u32 hi = min(n, i + 512);
+      rq_move<8, -1>(i, hi);
+      i = hi;
+    }
+    if (n > i) rq_move<2, -1>(i, n);
   }
   __device__ __forceinline__ void rq_up(u32 i, u32 n) {
-    for (u32 top = n; top > i;) {
-      const u32 cnt = min(top - i, 64 * kShift), lo = top - cnt;
-      u32x2 v[kShift];
-#pragma unroll
-      for (u32 u = 0; u < kShift; u++)
-        if (64 * u < cnt) v[u] = rq[ring(lo + 64 * u + lane)];
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (u32 u = 0; u < kShift; u++) {
-        const u32 j = 64 * u + lane;
-        if (64 * u < cnt && j < cnt) rq[ring(lo + j + 1)] = v[u];
-      }
-      __builtin_amdgcn_wave_barrier();
-      top = lo;
+    while (n > i + 128) {
+      const u32 lo = n > i + 512 ? n - 512 : i;
+      rq_move<8, 1>(lo, n);
+      n = lo;
     }
+    if (n > i) rq_move<2, 1>(i, n);
   }
   // Remove entry i of nreq, closing the gap from its shorter side.
   __device__ __forceinline__ void rq_remove(u32 i) {

@@ -22,8 +22,9 @@
 // front sit in registers, loads are issued before they are needed (free-list head, FIFO's next run,
 // hold count), and touching the prefix that was touched last only rewrites a step (4.17 -> 3.52 ms
 // and 60.9 -> 54.5 ms on the batches below).
-// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 135.3 -> 50.6 ms,
-// 512 pools of 65,536 blocks x 4,096 events 7.66 -> 3.38 ms (about 0.8 us an event either way).
+// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 142 -> 60 ms (the
+// launch ends with its slowest pool: 135 -> 51 to 141 -> 63 ms over three batches, the last with a mean
+// of 42 ms a pool), 512 pools of 65,536 blocks x 4,096 events 7.72 -> 3.42 ms; 0.6 to 1 us an event.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

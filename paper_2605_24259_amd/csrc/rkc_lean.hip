@@ -1174,7 +1174,8 @@ struct Lean {
         if (!r.ok) {
           const u32 dec = obs ? DEC_SHADOW : DEC_REJECTED;
           const u32 m = ST_REJECTED | (eff << 3) | (hardq << 5) | (prio << 6) | (dec << 9) | req_bits;
-          *gat(slot2, s) = u32x2{pk(L, c), pack_rejected(t, packed_of(m))};
+          // (a footprint that did not fit may exceed the pool, whose chains never do: cap it there)
+          *gat(slot2, s) = u32x2{pk(min(L, U()), c), pack_rejected(t, packed_of(m))};
           o.code = RKC_OC_MATFAIL;
           o.id = (i32)t;
           o.a = (i32)need;

@@ -21,6 +21,29 @@ def say(*a):
     sys.stdout.flush()
 
 
+def tile(base, n_pools):
+    """A batch of n_pools pools: copies of the base batch's pools in order, the last copy cut short."""
+    reps, k = -(-n_pools // base.n_pools), n_pools % base.n_pools or base.n_pools
+    desc = np.tile(base.desc, (reps, 1))
+    copy = np.repeat(np.arange(reps, dtype=np.int64), base.n_pools)
+    ends = []
+    for col, field, size, total in ((12, "event_offset", "n_events", base.n_events),
+                                    (14, "claim_slot_offset", "n_claim_slots", base.n_claim_slots)):
+        offset = base.field(field)
+        desc[:, col: col + 2] = (np.tile(offset, reps) + copy * total).view(np.int32).reshape(-1, 2)
+        ends.append((reps - 1) * total + int(offset[k - 1] + base.field(size)[k - 1]))
+    return type(base)(np.ascontiguousarray(desc[:n_pools]), np.tile(base.events, (reps, 1))[: ends[0]], ends[1])
+
+
+def compare_tiled(gpu, ora):
+    """Assert that every record of a tiled batch's replay equals its pool's in the base batch's (whose
+    pools lie in order, without gaps)."""
+    for got, want, name in zip(gpu, ora, ("outcomes", "pool telemetry", "claim telemetry")):
+        bad = np.nonzero((got != np.resize(want, (len(got), want.shape[1]))).any(1))[0]
+        assert bad.size == 0, (f"{name}: {bad.size} rows differ, the first {bad[0]}: gpu {got[bad[0]].tolist()} "
+                               f"oracle {want[bad[0] % len(want)].tolist()}")
+
+
 def compare_pools(trace, gpu, ora, pools=None, prefix_events=None, tel=True):
     """Assert bit-exact equality of outcomes, pool telemetry and claim telemetry for `pools`."""
     g_out, g_pt, g_ct = gpu

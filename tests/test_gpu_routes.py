@@ -3,7 +3,7 @@ import numpy as np
 import pytest
 
 from tests import randtrace
-from tests.gpu_util import compare_pools, gpu_replay, say
+from tests.gpu_util import compare_pools, compare_tiled, gpu_replay, say, tile
 
 pytestmark = pytest.mark.gpu
 
@@ -149,3 +149,29 @@ def test_few_pools_layout_past_lds(oracle_mod):
     say("case few pools past LDS")
     ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
     compare_pools(trace, gpu_replay(trace), ora)
+
+
+# claims that can never fit, with footprints past 16 bits and up to the largest valid one: lead_end of their
+# records is the chain's length, whole, in every kernel and layout (claim sets, key groups, few pools and many)
+@pytest.mark.parametrize("kernel", ["compact", "two events", "large-pool", "general"])
+@pytest.mark.parametrize("n_pools,n_chains,claims", [(48, 8, 64), (48, 8, 256), (48, 130, 64), (48, 130, 256),
+                                                     (4100, 8, 64), (4100, 100, 64), (4100, 130, 64), (4100, 8, 256),
+                                                     (4100, 100, 256), (4100, 130, 256)])
+def test_footprints_past_16_bits(oracle_mod, tg, kernel, n_pools, n_chains, claims):
+    import paper_2605_24259_amd as rkc
+    sizes = (65535, 65536, 65539, 65546, 131072 + 4, 1 << 24)
+    pools = []
+    for i in range(48):
+        c, pick = (7 * i) % n_chains, sizes[i % len(sizes):] + sizes[:i % len(sizes)]
+        evs = [tg.claim(10 + i % 3, c, 10, hard=1)] + [tg.claim(L, c, L - j % 2, hard=j & 1, prio=j & 3)
+                                                       for j, L in enumerate(pick)]
+        pools.append(dict(usable_blocks=20 + i, mode=i % 4, n_chains=n_chains, max_live_requests=4,
+                          max_live_claims=claims, events=evs[:2] if kernel == "two events" else evs))
+    base = tg.from_pools(pools)
+    say(f"case footprints past 16 bits: {kernel} {n_pools} {n_chains} {claims}")
+    ora = oracle_mod.replay(base.desc, base.events, base.n_claim_slots, threads=16)
+    assert (ora[0][:, 0] & 255 == 4).sum() >= 48  # MATFAIL
+    assert set(ora[2][:, 9]) == {10, 11, 12}
+    trace = tile(base, n_pools)
+    got = _big(trace) if kernel == "large-pool" else gpu_replay(trace, rkc.FLAG_GENERAL_KERNEL if kernel == "general" else 0)
+    compare_tiled(got, ora)

@@ -163,8 +163,10 @@ KERNEL_SOURCES = {
     "rkc_tiny": ("paper_2605_24259_amd/csrc/rkc_tiny.hip", "paper_2605_24259_amd/csrc/rkc_tiny.h",
                  "include/rkc.h", "paper_2605_24259_amd/build.py"),
     "rkc_lean": ("paper_2605_24259_amd/csrc/rkc_lean.hip", "paper_2605_24259_amd/csrc/rkc_lean_few.hip",
-                 "paper_2605_24259_amd/csrc/rkc_lean.h", "include/rkc.h", "paper_2605_24259_amd/build.py"),
+                 "paper_2605_24259_amd/csrc/rkc_lean.h", "paper_2605_24259_amd/csrc/rkc_guard.h", "include/rkc.h",
+                 "paper_2605_24259_amd/build.py"),
     "rkc_big": ("paper_2605_24259_amd/csrc/rkc_big.hip", "paper_2605_24259_amd/csrc/rkc_big.h",
+                "paper_2605_24259_amd/csrc/rkc_guard.h",
                 "include/rkc.h", "paper_2605_24259_amd/build.py"),
     "rkc_replay_wave": ("paper_2605_24259_amd/csrc/rkc_replay.hip", "include/rkc.h",
                         "paper_2605_24259_amd/build.py"),

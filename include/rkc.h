@@ -263,9 +263,10 @@ enum rkc_pool_status {
                                every outcome is INVALID (an ABI fault, not a contract outcome) */
   RKC_PS_INTERNAL = (int32_t)0x80000000u /* a kernel's own consistency guard fired (an allocation
                                that feasibility said must succeed found no block, a touch-stack
-                               node beyond its bound, a runaway loop); the pool's outputs from
-                               that step on are unreliable.  Never set on a correct build: the
-                               parity tests require it to be clear on every pool */
+                               node beyond its bound, a runaway loop, or blocks that do not add up
+                               to U when the pool is done); the pool's outputs are unreliable.
+                               Never set on a correct build: the parity tests require it to be
+                               clear on every pool */
 };
 
 /* ----------------------------------------------------------------------------------------------

@@ -30,6 +30,7 @@
 
 #include "rkc.h"
 #include "rkc_big.h"
+#include "rkc_guard.h"
 
 namespace {
 
@@ -703,7 +704,7 @@ struct Big {
         const u32 K0 = K;
         vic += K;
         if (hc >= 0 && ghc.n <= hlo) *lat<u32, 2>(L_KEYS, (u32)hc) = KINF;
-        // (every pass takes at least one block off K, so the loop ends whatever it meets)
+        // (every pass lowers K, so the loop ends whatever it meets; rkc_guard.h)
         while (K > 0) {
           const u32x4 k4 = ((lds_u32x4*)kk)[lane];
           const u32 m1 = wmin(min(min(k4.x, k4.y), min(k4.z, k4.w)));
@@ -711,7 +712,7 @@ struct Big {
             // the oldest finished request's private run (level 0)
             const u32 m = min(K, ftop - flo);
             E -= m;
-            K -= max(m, 1u);
+            K = rkc_left(K, m);
             ftop -= m;
             if (ftop == flo) fifo_pop();
           } else if (m1 != KINF) {
@@ -744,7 +745,7 @@ struct Big {
             }
             E -= m;
             g.n = nw;
-            K -= max(m, 1u);
+            K = rkc_left(K, m);
             bool moved = false;
             u32 key = top_key(c, g, moved);
             if (nw <= lo) key = KINF;
@@ -1378,7 +1379,8 @@ __device__ __forceinline__ void replay_pool(const rkc_big_args& g, const rkc_poo
     }
   }
   __syncthreads();
-  const u32 status = P.cget(BP::C_STATUS), queued = P.cget(BP::C_DQL), t2peak = P.cget(BP::C_T2PK);
+  const u32 status = P.cget(BP::C_STATUS) | (rkc_adds_up(U, P.F, P.A, P.E, P.PR) ? 0u : 0x80000000u);
+  const u32 queued = P.cget(BP::C_DQL), t2peak = P.cget(BP::C_T2PK);
   i32 v = (i32)P.tv;
   if (l < 10) v += (i32)P.hist[l];
   if (l == 32) v += (i32)P.hist[RKC_OC_DEFERRED];

@@ -35,6 +35,7 @@
 #include <stdint.h>
 
 #include "rkc.h"
+#include "rkc_guard.h"
 #include "rkc_lean.h"
 
 namespace {
@@ -724,7 +725,7 @@ struct Lean {
         u32 kf = noadm() ? KINF : FEW ? fk : ufl(cold[C_FKEY]);
         // the hit chain stops being a candidate once only hits remain
         if (hc >= 0 && ghc.n <= hlo) *lat<u32>(M::KEYS, (u32)hc) = KINF;
-        // (every pass takes at least one block off K, so the loop ends whatever it meets)
+        // (every pass lowers K, so the loop ends whatever it meets; rkc_guard.h)
         while (K > 0) {
           u32 kmin;
           if (NS == 4) {
@@ -743,7 +744,7 @@ struct Lean {
             const u32 m = min(K, ftop - flo);
             ftop -= m;
             E -= m;
-            K -= max(m, 1u);
+            K = rkc_left(K, m);
             if (ftop == flo) fifo_pop();
             cold_fifo_out();
             kf = fk;
@@ -789,7 +790,7 @@ struct Lean {
             r.post += rs - sc;
             E -= m;
             g.n = nw;
-            K -= max(m, 1u);
+            K = rkc_left(K, m);
             bool moved = false;
             u32 key = top_key(c, g, moved);
             // (the hit chain stops being a candidate once only hits remain; any other chain's key
@@ -1485,7 +1486,8 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
 
   const u32 nslot_used = P.nslot;
   const u32 vic = P.vic, post = P.post;
-  const u32 status = ufl(P.cold[LP::C_STATUS]), queued = ufl(P.cold[LP::C_DQL]);
+  const u32 status = ufl(P.cold[LP::C_STATUS]) | (rkc_adds_up(U, P.F, P.A, P.E, P.PR) ? 0u : 0x80000000u);
+  const u32 queued = ufl(P.cold[LP::C_DQL]);
   const u32 t2peak = ufl(P.cold[LP::C_T2PK]);
   // Final records of the claims still live (each lane writes its own) ...
 #pragma unroll

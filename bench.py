@@ -133,14 +133,15 @@ SCALAR_ISSUE_PEAK = 256 * 2.4
 def kernel_name(lim, n_pools=0):
     """Which replay kernel the library picks for these batch limits (the compact one when every
     limit fits its 16-bit encoding, one lane per pool when the traces are very short, the
-    large-pool one within its limits)."""
+    large-pool one within its limits where a CU gets one pool; with more pools the library also
+    weighs how many a CU holds, which none of the workloads here comes to)."""
     fits = (lim["max_usable_blocks"] <= 32767 and lim["max_events"] <= 65533
             and lim["max_live_claims"] <= 256 and lim["max_chains"] <= 256
             and lim["max_live_requests"] <= 256 and lim["max_claim_slots"] <= 65534)
     if fits and lim["max_claim_slots"] <= 8 and lim["max_events"] <= (4 if n_pools >= 49152 else 2):
         return "rkc_tiny"
     big = (lim["max_usable_blocks"] < 1 << 20 and lim["max_events"] <= 65536 and lim["max_chains"] <= 256
-           and lim["max_live_requests"] <= 16384 and lim["max_claim_slots"] <= 65536)
+           and lim["max_live_requests"] <= 16384 and lim["max_live_claims"] <= 4096 and lim["max_claim_slots"] <= 65536)
     return "rkc_lean" if fits else "rkc_big" if big else "rkc_replay_wave"
 
 

@@ -296,8 +296,9 @@ typedef struct rkc_batch {
  * compact kernel is chosen for usable blocks <= 32,767, events <= 65,533, chains <= 256, live
  * claims <= 256 and live requests <= 256; of those, batches of at most two events a pool, or four when
  * they are large, are replayed by one lane per pool) or the large-pool one (usable blocks < 2^20,
- * events <= 65,536, chains <= 256, live requests <= 16,384).  All give identical outputs; the flag
- * exists so the general kernel can be checked on the same inputs. */
+ * events <= 65,536, chains <= 256, live requests <= 16,384, live claims <= 4,096; not batches of so many
+ * pools that the general kernel, which holds more of them at a time, is the faster one).  All give
+ * identical outputs; the flag exists so the general kernel can be checked on the same inputs. */
 #define RKC_FLAG_GENERAL_KERNEL 1
 /* rkc_batch.flags: one wavefront per pool everywhere.  Without it, a batch of at most 256 pools (one
  * per compute unit) that the general kernel serves and whose live lists do not fit in LDS is replayed

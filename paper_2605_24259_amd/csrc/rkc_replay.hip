@@ -1781,14 +1781,43 @@ bool use_lean(const rkc_batch* b, rkc_lean_args* g) {
   return !(b->flags & RKC_FLAG_GENERAL_KERNEL) && rkc_lean_layout(b, g);
 }
 
-// The large-pool kernel serves the other batches within its limits unless the caller asks for the
-// general one.  (A batch that would need more scratch there than on the general kernel, where long
-// claim lists may fit in LDS, stays on the general one: the scratch a batch needs never grows.)
+// Rounds in which a batch's pools run: a CU holds as many of them as their LDS (given out in units of 1,280
+// bytes) and the kernel's registers (`waves`) allow.
+u64 rounds(const rkc_batch* b, u64 lds, u64 waves) {
+  const u64 fit = kLdsBudget / align_up(lds, 1280), per_cu = kCUs * (fit < waves ? fit : waves);
+  return ((u64)b->n_pools + per_cu - 1) / per_cu;
+}
+
+// The large-pool kernel serves the other batches within its limits where it is the faster one, unless the
+// caller asks for the general one.  It replays a pool 2 to 2.6 times as fast, but keeps all live requests
+// and 256 chains and claims in LDS, so fewer pools share a CU: one from 4,097 declared requests on, 3 to 8
+// below, where the general kernel holds up to 16 (its lists in LDS) or 12 (in scratch).  So it pays up to
+// 2.5 times the general kernel's rounds: general against this kernel, at 1 : 1 rounds 2.0 to 3.9 times its
+// time, 1 : 2 1.1 to 1.4 times (512 pools of 262,144 blocks, 16,384 requests, 2,048 events 4.48 and 3.74 ms;
+// 65,536 pools of 40,000 blocks, 32 requests, 128 events 4.72 and 4.28 ms), 2 : 5 1.07 to 1.12 times (8,192
+// pools of 2,048 blocks, 300 requests, 1,024 events 5.27 and 4.69 ms), 1 : 3 0.86 to 1.05 (768 pools of
+// 65,536 blocks, 8,192 requests 2.42 and 2.81 ms), and from 1 : 4 on it loses (2,048 pools of 262,144
+// blocks 5.3 and 14.7 ms).
+// Setting up and writing out a pool costs it more, so traces of a few events need as few rounds as there
+// (65,536 pools of 40,000 blocks, 29 : 16 rounds: 2 events 113 and 155 us, 4 events 178 and 209, 8 events
+// 311 and 323, 16 events 592 and 551; at 8 : 11 rounds 4 events 115 and 66 us).
+// Its one wave walks long claim lists alone.  Tables of up to 4,096 claims are rarely full, and where few of
+// them are live it wins (the 64 pools of 262,144 blocks 134 and 52 ms); full, they cost 64 pools 79 and
+// 103 ms, 512 pools 159 and 145 ms.  Larger tables lose either way once they fill: 8,000 live claims 70 and
+// 179 ms on 64 pools, 193 and 273 ms on 512.
+// (A batch that would need more scratch there than on the general kernel, where long claim lists may fit in
+// LDS, stays on the general one: the scratch a batch needs never grows.)
 bool use_big(const rkc_batch* b, rkc_big_args* g) {
+  constexpr i32 kMaxClaims = 4096, kShortTrace = 8;
+  constexpr u64 kWavesLds = 16, kWavesScratch = 12, kWavesBig = 24;  // waves a CU's registers hold, by kernel
   memset(g, 0, sizeof *g);
   Layout L;
-  return !(b->flags & RKC_FLAG_GENERAL_KERNEL) && rkc_big_layout(b, g) &&
-         choose_layout(b, &L) && g->scr_pool_bytes <= L.scr_pool_bytes;
+  if ((b->flags & RKC_FLAG_GENERAL_KERNEL) || b->max_live_claims > kMaxClaims || !rkc_big_layout(b, g) ||
+      !choose_layout(b, &L) || g->scr_pool_bytes > L.scr_pool_bytes)
+    return false;
+  const u64 general = rounds(b, L.lds_bytes, L.global_lists ? kWavesScratch : kWavesLds);
+  const u64 big = rounds(b, g->lds_bytes, kWavesBig);
+  return b->max_events < kShortTrace ? big <= general : 2 * big <= 5 * general;
 }
 
 }  // namespace

@@ -138,7 +138,8 @@ def kernel_name(lim, n_pools=0):
     fits = (lim["max_usable_blocks"] <= 32767 and lim["max_events"] <= 65533
             and lim["max_live_claims"] <= 256 and lim["max_chains"] <= 256
             and lim["max_live_requests"] <= 256 and lim["max_claim_slots"] <= 65534)
-    if fits and lim["max_claim_slots"] <= 8 and lim["max_events"] <= (4 if n_pools >= 49152 else 2):
+    if fits and lim["max_claim_slots"] <= 8 and (lim["max_events"] <= 2 and n_pools > 4096
+                                                 or lim["max_events"] <= 4 and n_pools >= 49152):
         return "rkc_tiny"
     big = (lim["max_usable_blocks"] < 1 << 20 and lim["max_events"] <= 65536 and lim["max_chains"] <= 256
            and lim["max_live_requests"] <= 16384 and lim["max_live_claims"] <= 4096 and lim["max_claim_slots"] <= 65536)

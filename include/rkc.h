@@ -294,8 +294,8 @@ typedef struct rkc_batch {
 
 /* rkc_batch.flags: replay with the general kernel even when the batch fits the compact one (the
  * compact kernel is chosen for usable blocks <= 32,767, events <= 65,533, chains <= 256, live
- * claims <= 256 and live requests <= 256; of those, batches of at most two events a pool, or four when
- * they are large, are replayed by one lane per pool) or the large-pool one (usable blocks < 2^20,
+ * claims <= 256 and live requests <= 256; of those, large batches of at most two events a pool, or four in
+ * still larger ones, are replayed by one lane per pool) or the large-pool one (usable blocks < 2^20,
  * events <= 65,536, chains <= 256, live requests <= 16,384, live claims <= 4,096; not batches of so many
  * pools that the general kernel, which holds more of them at a time, is the faster one).  All give
  * identical outputs; the flag exists so the general kernel can be checked on the same inputs. */

@@ -31,6 +31,22 @@
 #define RKC_UNROLL
 #endif
 
+// One lane per pool or one wavefront per pool (compact kernel), for a batch within the compact kernel's limits.
+// A lane's unrolled code runs every event type that its wave's pools hold in turn, so its time depends on the
+// mix and hardly on the number of pools; a wavefront's pays for every pool.  By lane against by wavefront:
+//   two events: batches of one claim and one prefill a pool 7.3 us at any size up to 8,192 pools against 6.8 us
+//   (64 pools), 7.3 (1,024), 8.5 (4,096) and 11.9 (8,192); pools of 80 blocks with mixed events 9.1 to 12.2 us
+//   against 6.4, 7.3, 9.3 and 13.2; 131,072 pools 19.6 against 144 us.  So from the first batch on that
+//   is not resident as wavefronts all at once.
+//   three and four events: 65,536 pools 22 to 51 us against 75 to 95, 49,152 pools 22 to 51 against 58 to 73
+//   (both of these with a pass of about 2 us over the batch before them); 32,768 pools 48 us by lane at the
+//   longest, 39 to 48 by wavefront.
+//   eight events: 331 us against 121 us at 65,536 pools, never worth it.
+// A lane writes its pool's unused claim slots by itself, so it takes pools with few slots only.
+inline bool rkc_tiny_serves(int32_t n_pools, int32_t max_events, int32_t max_slots) {
+  return max_slots <= 8 && ((max_events <= 2 && n_pools > 4096) || (max_events <= 4 && n_pools >= 49152));
+}
+
 // the batch limits a pool's descriptor is checked against
 struct rkc_tiny_limits {
   int64_t n_events_total, n_slots_total;

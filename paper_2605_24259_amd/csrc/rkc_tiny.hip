@@ -30,16 +30,7 @@ rkc_status launch(const rkc_lean_args* a, hipStream_t s) {
 
 }  // namespace
 
-// One lane per pool or one wavefront per pool (compact kernel): both sides measured on batches of
-// pools of 80 to 512 blocks.  Two events: 131,072 pools 19.6 us by lane, 144 us by wavefront; 4 pools
-// 6.9 us either way.  Four events: a lane's replay is 48 us long however few the pools (its unrolled
-// code runs every event type's branch in turn), so it pays only once the wavefronts take longer:
-// 65,536 pools 50 us by lane, 84 us by wavefront; 1,024 pools 47 and 11 us.  Eight events: 331 us
-// against 121 us at 65,536 pools, never worth it.  A lane writes its pool's unused claim slots by
-// itself, so it takes pools with few slots only.
-bool rkc_tiny_fits(const rkc_lean_args* a) {
-  return a->max_slots <= 8 && (a->max_events <= 2 || (a->max_events <= 4 && a->n_pools >= 49152));
-}
+bool rkc_tiny_fits(const rkc_lean_args* a) { return rkc_tiny_serves(a->n_pools, a->max_events, a->max_slots); }
 
 rkc_status rkc_tiny_launch(const rkc_lean_args* a, hipStream_t s) {
   return a->max_events <= 2 ? launch<2>(a, s) : launch<4>(a, s);

@@ -20,6 +20,9 @@ extern "C" void tiny_replay(int e, int n, const rkc_tiny_limits* g, const rkc_po
     else rkc_tiny_pool<4>(*g, d[i], ev, o, p + i, c);
   }
 }
+extern "C" int tiny_serves(int n_pools, int max_events, int max_slots) {
+  return rkc_tiny_serves(n_pools, max_events, max_slots);
+}
 """
 
 
@@ -73,3 +76,12 @@ def test_tiny_replay_of_the_capacity_sweep(oracle_mod, host_lib, tg):
     ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=8)
     for g, o in zip(host_replay(host_lib, trace, 2), ora[:3]):
         assert np.array_equal(g, o)
+
+
+# a lane replays its pools' event types in turn: batches that are resident as wavefronts all at once are
+# faster that way (64 pools of two mixed events 6.4 us, by lane 10 us)
+@pytest.mark.parametrize("n_pools,events,slots,lane", [
+    (1, 2, 8, 0), (64, 2, 8, 0), (4096, 2, 8, 0), (4097, 2, 8, 1), (131072, 1, 1, 1), (4097, 2, 9, 0),
+    (4097, 3, 8, 0), (49151, 4, 8, 0), (49152, 3, 8, 1), (49152, 4, 8, 1), (49152, 5, 8, 0)])
+def test_batches_of_the_lane_per_pool_replay(host_lib, n_pools, events, slots, lane):
+    assert host_lib.tiny_serves(n_pools, events, slots) == lane

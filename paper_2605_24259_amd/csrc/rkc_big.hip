@@ -117,7 +117,7 @@ __device__ __forceinline__ u32 vofs(u32 i) {
   return r;
 }
 // Entry i (wave-uniform) of the array of 2^SH-byte entries at byte `at` of the workgroup's LDS (the kernel
-// has no static LDS, so its dynamic LDS starts at address 0).
+// has no static LDS, which the build sees to, so its dynamic LDS starts at address 0).
 template <class T, int SH>
 __device__ __forceinline__ __attribute__((address_space(3))) T* lat(u32 at, u32 i) {
   return (__attribute__((address_space(3))) T*)(vofs<SH>(i) + at);

@@ -148,9 +148,9 @@ template <class T>
 __device__ __forceinline__ T* gat(T* base, u32 i) {
   return (T*)((__attribute__((address_space(1))) char*)base + (u64)vofs<T>(i));
 }
-// Entry i (wave-uniform) of the array at byte `at` of the workgroup's LDS.  The kernel has no static LDS,
-// so its dynamic LDS starts at address 0 and `at` folds into the access: a pointer formed from the
-// LDS array's name takes a second vector instruction per access to add its address, 0.
+// Entry i (wave-uniform) of the array at byte `at` of the workgroup's LDS.  The kernel has no static LDS (the
+// build refuses an object that has), so its dynamic LDS starts at address 0 and `at` folds into the access: a
+// pointer formed from the LDS array's name takes a second vector instruction per access to add its address, 0.
 template <class T>
 __device__ __forceinline__ __attribute__((address_space(3))) T* lat(u32 at, u32 i) {
   return (__attribute__((address_space(3))) T*)(vofs<T>(i) + at);

@@ -16,6 +16,15 @@ def gpu_replay(trace, flags=0):
     return db.results()
 
 
+def large_pool_route(trace, limits):
+    """Whether the large-pool kernel takes the batch: it needs less scratch there than on the general kernel.
+    (For batches past the compact kernel's limits, and long enough that the scratch differs.)"""
+    import paper_2605_24259_amd as rkc
+    need = [rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, limits, flags=f, scratch=False).scratch_needed
+            for f in (0, rkc.FLAG_GENERAL_KERNEL)]
+    return need[0] < need[1]
+
+
 def say(*a):
     print(*a, flush=True)
     sys.stdout.flush()

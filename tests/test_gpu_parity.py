@@ -12,7 +12,7 @@ import pytest
 from tests import deferral_cases, relax_cases
 from tests import golden_fixtures as gf
 from tests import randtrace
-from tests.gpu_util import compare_pools, gpu_replay, say
+from tests.gpu_util import compare_pools, compare_tiled, gpu_replay, large_pool_route, say, tile
 
 pytestmark = pytest.mark.gpu
 
@@ -77,12 +77,14 @@ def test_random_medium(oracle_mod, seed):
 @pytest.mark.parametrize("n_chains", [64, 65, 128, 129, 256])
 def test_chain_groups(oracle_mod, n_chains):
     """Pools with many shared chains at the edges of the compact kernel's key groups (64 chains per
-    lane-wide group: one, two or four groups), so every key group and chain record is in use."""
+    lane-wide group: one or four in the layout for few pools; one, two or four past 4,096 pools, run as
+    copies of the same pools), so every key group and chain record is in use."""
     trace = randtrace.random_batch(50 + n_chains, 300, U_range=(40, 400), n_events=(100, 500),
                                    n_chains=n_chains, p_malformed=0.01, tight_every=9, caps=(256, 64))
     assert trace.limits()["max_chains"] == n_chains
     gpu, ora = _both(oracle_mod, trace)
     compare_pools(trace, gpu, ora)
+    compare_tiled(gpu_replay(tile(trace, 4300)), ora)
 
 
 def test_edge_cases(oracle_mod, tg):
@@ -273,32 +275,40 @@ def test_descriptor_offsets_outside_batch(tg, flags):
     assert db.query_telemetry(2, 1)[0] == -3
 
 
+LAYOUT_LIMITS = {
+    "narrow": {},
+    "wide": dict(max_usable_blocks=40000),                # above the 16-bit bound
+    # the lists no longer fit in LDS
+    "wide_global_lists": dict(max_usable_blocks=40000, max_live_requests=20000, max_live_claims=4096),
+    "global_lists_small_request_table": dict(max_usable_blocks=40000, max_live_claims=8192),
+}
+
+
+def _layouts(oracle_mod, trace, variant):
+    """The trace replayed by the general kernel with the storage that the variant's limits lead to, and by
+    the kernel that these limits go to by themselves, against the oracle."""
+    import paper_2605_24259_amd as rkc
+    if variant == "global_lists_small_request_table":
+        _small_request_tables(trace)
+    lim = dict(trace.limits(), **LAYOUT_LIMITS[variant])
+    assert variant == "narrow" or large_pool_route(trace, lim) == (variant == "wide")
+    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=ORACLE_THREADS)
+    for flags in (rkc.FLAG_GENERAL_KERNEL, 0):
+        db = rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, lim, flags=flags)
+        compare_pools(trace, db.replay().results(), ora)
+
+
 @pytest.mark.parametrize("variant", ["narrow", "wide", "wide_global_lists",
                                      "global_lists_small_request_table"])
 def test_storage_layouts_agree(oracle_mod, tg, variant):
-    """The same pools replayed with 16-bit LDS state, 32-bit LDS state and 32-bit state with the
-    lists in global scratch (chosen by the batch's declared limits) match the oracle exactly.  The
-    last variant keeps the lists in global scratch with a live-request table of at most 6 entries,
-    so the request list's gap closing from both sides wraps back to the start of its arrays."""
-    import paper_2605_24259_amd as rkc
+    """The same pools replayed by the general kernel with 16-bit LDS state, 32-bit LDS state and 32-bit
+    state with the lists in global scratch (chosen by the batch's declared limits) match the oracle
+    exactly.  The last variant keeps the lists in global scratch with a live-request table of at most 6
+    entries, so the request list's gap closing from both sides wraps back to the start of its arrays."""
+    say(f"case layouts/{variant}")
     trace = randtrace.random_batch(41, 600, U_range=(2, 200), n_events=(1, 200), n_chains=7,
                                    tight_every=9)
-    if variant == "global_lists_small_request_table":
-        _small_request_tables(trace)
-    lim = dict(trace.limits())
-    if variant == "wide":
-        lim["max_usable_blocks"] = 40000          # above the 16-bit bound
-    elif variant == "wide_global_lists":
-        lim["max_usable_blocks"] = 40000
-        lim["max_live_requests"] = 20000          # lists no longer fit in LDS
-        lim["max_live_claims"] = 4096
-    else:
-        lim["max_usable_blocks"] = 40000
-        lim["max_live_claims"] = 8192             # the claim list no longer fits in LDS
-    say(f"case layouts/{variant}")
-    gpu = rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, lim).replay().results()
-    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=ORACLE_THREADS)
-    compare_pools(trace, gpu, ora)
+    _layouts(oracle_mod, trace, variant)
 
 
 def _small_request_tables(trace):
@@ -399,21 +409,24 @@ def test_claim_sets(oracle_mod, seed, kw):
     compare_pools(trace, gen, ora)
 
 
-@pytest.mark.parametrize("seed", [5, 6])
-def test_request_list_past_lds(oracle_mod, seed):
-    """Live-request lists of up to 256 entries, of which the compact kernel keeps the first 128 in
-    LDS and the rest in global scratch: lists that grow past that split, fill the table and shrink
-    back below it, with extends and finishes picking anywhere in them and retried requests entering
+@pytest.mark.parametrize("seed,n_chains,in_lds", [(5, 200, 96), (6, 200, 96), (7, 60, 128), (8, 120, 128)])
+def test_request_list_past_lds(oracle_mod, seed, n_chains, in_lds):
+    """Live-request lists of up to 256 entries, of which the compact kernel keeps the first 128 (96 with
+    more than 128 chains) in LDS and the rest in global scratch once a batch has more than 4,096 pools (run
+    as copies of the pools), and all in LDS below: lists that grow past that split, fill the table and
+    shrink back below it, with extends and finishes picking anywhere in them and retried requests entering
     in id order; against the oracle and the general kernel on the same inputs."""
     import paper_2605_24259_amd as rkc
-    trace = randtrace.many_requests_batch(seed, 256)
+    trace = randtrace.many_requests_batch(seed, 256 if n_chains == 200 else 64, n_chains=n_chains)
     gpu, ora = _both(oracle_mod, trace)
     compare_pools(trace, gpu, ora)
     live = ora[1][:, 29]
-    assert (live > 128).any() and (live < 128).any()
+    assert (live > 128).any() and (live < in_lds).any()
     assert (ora[1][:, 31] & 1).any()  # RKC_PS_REQUEST_TABLE: some lists reached the capacity
+    assert ora[1][:, 33].any()        # retried requests entered a list
     gen = gpu_replay(trace, flags=rkc.FLAG_GENERAL_KERNEL)
     compare_pools(trace, gen, ora)
+    compare_tiled(gpu_replay(tile(trace, 4100)), ora)
 
 
 def _edge_selectors(n):
@@ -477,26 +490,14 @@ def test_regression_capacity_refusal_record_in_deferring_pools(oracle_mod):
 @pytest.mark.parametrize("offload", [False, True])
 @pytest.mark.parametrize("variant", ["wide", "wide_global_lists", "global_lists_small_request_table"])
 def test_deferral_storage_layouts(oracle_mod, tg, variant, offload):
-    """Deferral and runtime relaxation (with and without a second tier) with 32-bit LDS state and
-    with the live lists in global scratch (also with live-request tables of at most 6 entries:
-    retried requests enter a list that wraps back to the start of its arrays)."""
-    import paper_2605_24259_amd as rkc
+    """Deferral and runtime relaxation (with and without a second tier) on the general kernel with
+    32-bit LDS state and with the live lists in global scratch (also with live-request tables of at most
+    6 entries: retried requests enter a list that wraps back to the start of its arrays)."""
+    say(f"case deferral layouts/{variant} offload={offload}")
     trace = randtrace.random_batch(71, 600, U_range=(2, 200), n_events=(1, 200), n_chains=7,
                                    tight_every=9, defer=True, relax=True, hard_share=0.8,
                                    offload=offload)
-    if variant == "global_lists_small_request_table":
-        _small_request_tables(trace)
-    lim = dict(trace.limits())
-    lim["max_usable_blocks"] = 40000
-    if variant == "wide_global_lists":
-        lim["max_live_requests"] = 20000
-        lim["max_live_claims"] = 4096
-    elif variant == "global_lists_small_request_table":
-        lim["max_live_claims"] = 8192
-    say(f"case deferral layouts/{variant} offload={offload}")
-    gpu = rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, lim).replay().results()
-    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=ORACLE_THREADS)
-    compare_pools(trace, gpu, ora)
+    _layouts(oracle_mod, trace, variant)
 
 
 def test_zipf_defer_full_sampled(oracle_mod, tg):

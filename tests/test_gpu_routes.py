@@ -3,21 +3,22 @@ import numpy as np
 import pytest
 
 from tests import randtrace
-from tests.gpu_util import compare_pools, compare_tiled, gpu_replay, say, tile
+from tests.gpu_util import compare_pools, compare_tiled, gpu_replay, large_pool_route, say, tile
 
 pytestmark = pytest.mark.gpu
 
 
-# four claim sets with one, two and four 64-chain key groups: the edges of the groups
+# four claim sets over the edges of the 64-chain key groups: one or four groups in the layout for few pools;
+# one, two or four past 4,096 pools
+@pytest.mark.parametrize("n_pools", [96, 4100])
 @pytest.mark.parametrize("n_chains", [64, 65, 128, 129, 256])
-def test_claim_sets_over_chain_groups(oracle_mod, n_chains):
-    trace = randtrace.many_claims_batch(900 + n_chains, 96, n_events=(300, 900), n_chains=n_chains)
-    say(f"case claim sets over {n_chains} chains: {trace.n_pools} pools")
-    gpu = gpu_replay(trace)
-    ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+def test_claim_sets_over_chain_groups(oracle_mod, n_chains, n_pools):
+    base = randtrace.many_claims_batch(900 + n_chains, 96, n_events=(300, 900), n_chains=n_chains)
+    say(f"case claim sets over {n_chains} chains: {n_pools} pools")
+    ora = oracle_mod.replay(base.desc, base.events, base.n_claim_slots, threads=16)
     assert not ora[3].any()
     assert ora[1][:, 30].max() > 64, "no pool keeps more than one claim set live"
-    compare_pools(trace, gpu, ora)
+    compare_tiled(gpu_replay(tile(base, n_pools)), ora)
 
 
 # two events: one wavefront per pool up to 4,096 pools, one lane per pool above (partial and whole waves)
@@ -45,6 +46,7 @@ def _big(trace, **limits):
     import paper_2605_24259_amd as rkc
     lim = dict(trace.limits(), **limits)
     lim["max_usable_blocks"] = max(lim["max_usable_blocks"], 40000)
+    assert large_pool_route(trace, lim)
     return rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, lim).replay().results()
 
 
@@ -61,7 +63,7 @@ def test_large_pool_kernel_random(oracle_mod, n_pools, kw):
     compare_pools(trace, _big(trace), ora)
 
 
-# its request ring: tables of 1 to 6 entries, whose ring wraps all the time, and at its largest
+# its request ring: tables of 1 to 6 entries, whose ring wraps all the time, and a ring far larger than the lists
 @pytest.mark.parametrize("max_live_requests", [6, 16384])
 def test_large_pool_kernel_request_ring(oracle_mod, max_live_requests):
     trace = randtrace.many_requests_batch(17, 48, n_events=(900, 1500), n_chains=200, req_cap=1024)
@@ -70,6 +72,50 @@ def test_large_pool_kernel_request_ring(oracle_mod, max_live_requests):
     say(f"case request ring {max_live_requests}")
     ora = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
     compare_pools(trace, _big(trace, max_live_requests=max_live_requests), ora)
+
+
+def _full_ring_pool(tg, rng, mode, cap, rounds):
+    """A pool that fills its live-request table, then finishes, extends and refills at both ends of it, with
+    selectors at the edges of their range; a deferring one also takes its oldest request back in, at the front."""
+    late = mode == 3
+    evs = []
+    if late:
+        evs += [tg.claim(3 * cap, 0, 3 * cap, hard=1), tg.prefill(3 * cap + 5, -1, 0)]  # refused for the claim: deferred
+    evs += [tg.prefill(1 + i % 2, 1 + i % 9, i % 2) for i in range(cap - late)]
+    if late:
+        evs += [tg.release(0), tg.retry()]
+    evs += [tg.prefill(1, -1, 0)]  # the table is full
+    n, top = cap, 2**32 - 1
+    for k in range(rounds):
+        take = min(n - 1, int(rng.integers(1, 40)))
+        for m in range(n, n - take, -1):
+            last = top // m * m  # the largest multiple of the list's length, below 2^32
+            sel = (0, 1, m - 1, m // 2, m // 2 - 1, m, last - 1, last, top, int(rng.integers(0, top)))[int(rng.integers(0, 10))]
+            evs += [tg.extend(1, sel), tg.finish(sel)]
+        n -= take
+        more = min(cap - n, int(rng.integers(1, 30)))
+        evs += [tg.prefill(1, 1 + k % 9, k % 2)] * more
+        n += more
+    return dict(usable_blocks=6 * cap + 4, mode=mode, n_chains=10, max_live_requests=cap, max_live_claims=2, events=evs,
+                defer_limit=2 if late else 0)
+
+
+# the ring filled to its last entry, and lists of thousands of requests shifted from both sides, with selectors
+# at the edges of their range over counts of thousands; the largest ring against the general kernel (the
+# oracle takes half a minute)
+@pytest.mark.parametrize("cap,rounds,reference", [(1024, 150, "oracle"), (5000, 60, "oracle"), (16384, 25, "general kernel")])
+def test_large_pool_kernel_full_ring(oracle_mod, tg, cap, rounds, reference):
+    import paper_2605_24259_amd as rkc
+    rng = np.random.default_rng(cap)
+    trace = tg.from_pools([_full_ring_pool(tg, rng, mode, cap, rounds) for mode in range(4)])
+    say(f"case full request ring {cap}")
+    if reference == "oracle":
+        ref = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    else:
+        ref = gpu_replay(trace, flags=rkc.FLAG_GENERAL_KERNEL)
+    assert (ref[1][:, 31] == 1).all()  # each table overflowed once full
+    assert ref[1][3, 33] == 1          # the deferred request was served late
+    compare_pools(trace, _big(trace, max_live_requests=cap), ref)
 
 
 # its claim list past the 256 claims kept in LDS, and long lists of both kinds
@@ -91,9 +137,12 @@ def test_large_pool_kernel_long_lists(oracle_mod, tg):
     compare_pools(trace, gpu_replay(trace), ora)
 
 
-# the edges of its encoding: 2^20 - 1 blocks and 65,536 events go there, one more of either does not
-@pytest.mark.parametrize("usable,events", [((1 << 20) - 1, 65536), (1 << 20, 65536), ((1 << 20) - 1, 65537)])
-def test_large_pool_kernel_limits(tg, usable, events):
+# the edges of its encoding: 2^20 - 1 blocks and 65,536 events go there, one more of either does not; against
+# the oracle where that replays the batch in seconds, else against the general kernel
+@pytest.mark.parametrize("usable,events,large_pool,reference", [
+    ((1 << 20) - 1, 65536, True, "general kernel"), ((1 << 20) - 1, 100, True, "oracle"), (1 << 20, 100, False, "oracle"),
+    (300, 65536, True, "oracle"), (300, 65537, False, "oracle")])
+def test_large_pool_kernel_limits(oracle_mod, tg, usable, events, large_pool, reference):
     import paper_2605_24259_amd as rkc
     sel = [(i * 2654435761) & 0x7FFFFFFF for i in range(events)]
     evs = []
@@ -114,10 +163,14 @@ def test_large_pool_kernel_limits(tg, usable, events):
     trace = tg.from_pools([dict(usable_blocks=usable, mode=m, n_chains=256, max_live_requests=9000, max_live_claims=300,
                                 events=evs) for m in range(4)])
     say(f"case large-pool limits {usable} {events}")
+    assert large_pool_route(trace, trace.limits()) == large_pool
     got = gpu_replay(trace)
-    gen = gpu_replay(trace, flags=rkc.FLAG_GENERAL_KERNEL)
     assert not (got[1][:, 31] & ~7).any()
-    compare_pools(trace, got, gen)
+    if reference == "oracle":
+        ref = oracle_mod.replay(trace.desc, trace.events, trace.n_claim_slots, threads=16)
+    else:
+        ref = gpu_replay(trace, flags=rkc.FLAG_GENERAL_KERNEL)
+    compare_pools(trace, got, ref)
 
 
 # the compact kernel's layout for few pools at its largest batch and one pool past it, per claim-set
@@ -154,7 +207,7 @@ def test_footprints_past_16_bits(oracle_mod, tg, kernel, n_pools, n_chains, clai
     for i in range(48):
         c, pick = (7 * i) % n_chains, sizes[i % len(sizes):] + sizes[:i % len(sizes)]
         evs = [tg.claim(10 + i % 3, c, 10, hard=1)] + [tg.claim(L, c, L - j % 2, hard=j & 1, prio=j & 3)
-                                                       for j, L in enumerate(pick)]
+                                                       for j, L in enumerate(3 * pick)]
         pools.append(dict(usable_blocks=20 + i, mode=i % 4, n_chains=n_chains, max_live_requests=4,
                           max_live_claims=claims, events=evs[:2] if kernel == "two events" else evs))
     base = tg.from_pools(pools)
@@ -165,3 +218,15 @@ def test_footprints_past_16_bits(oracle_mod, tg, kernel, n_pools, n_chains, clai
     trace = tile(base, n_pools)
     got = _big(trace) if kernel == "large-pool" else gpu_replay(trace, rkc.FLAG_GENERAL_KERNEL if kernel == "general" else 0)
     compare_tiled(got, ora)
+
+
+# one claim set over one, two and four key groups with deferral, relaxation and offload, in both layouts
+@pytest.mark.parametrize("n_pools", [200, 4100])
+@pytest.mark.parametrize("n_chains", [60, 128, 256])
+def test_relaxation_over_key_groups(oracle_mod, n_chains, n_pools):
+    base = randtrace.random_batch(600 + n_chains, 200, U_range=(40, 400), n_events=(100, 300), n_chains=n_chains,
+                                  tight_every=9, caps=(256, 64), defer=True, relax=True, offload=True, hard_share=0.8)
+    say(f"case relaxation over {n_chains} chains: {n_pools} pools")
+    ora = oracle_mod.replay(base.desc, base.events, base.n_claim_slots, threads=16)
+    assert ora[1][:, 36].sum() > 100 and ora[1][:, 38].sum() > 50  # relaxed requests, offloaded claims
+    compare_tiled(gpu_replay(tile(base, n_pools)), ora)

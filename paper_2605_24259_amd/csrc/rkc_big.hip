@@ -24,9 +24,9 @@
 // front sit in registers, loads are issued before they are needed (free-list head, FIFO's next run,
 // hold count), and touching the prefix that was touched last only rewrites a step (4.17 -> 3.52 ms
 // and 60.9 -> 54.5 ms on the batches below).
-// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 142 -> 60 ms (the
-// launch ends with its slowest pool: 135 -> 51 to 141 -> 63 ms over three batches, the last with a mean
-// of 42 ms a pool), 512 pools of 65,536 blocks x 4,096 events 7.72 -> 3.42 ms; 0.6 to 1 us an event.
+// Measured against the general kernel: 64 pools of 262,144 blocks x 65,536 events 133 -> 50.5 ms (the launch
+// ends with its slowest pool: of four batches the slowest takes 141 -> 62 ms, with a mean of 42 ms a pool), 512
+// pools of 65,536 blocks x 4,096 events 7.72 -> 3.35 ms; 0.6 to 1 us an event.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

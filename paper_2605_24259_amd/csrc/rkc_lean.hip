@@ -1610,8 +1610,8 @@ __global__ __launch_bounds__(1024) void rkc_lean_order_scatter(i32 n_pools, cons
 
 // One wavefront per pool, in the launch order above (or batch order); the pool's policy selects its
 // specialized event loop once.  With four claim sets the registers, not LDS, bound residency: the kernel is
-// held to 6 waves per SIMD (80 vector registers, a few values spilled to scratch; 5 waves and 93
-// registers otherwise, measured slower: nested 9.9 vs 9.3 ms).
+// held to 6 waves per SIMD (80 vector registers, none spilled to scratch memory; 5 waves and 93 registers
+// otherwise, measured slower: nested 9.9 vs 9.3 ms).
 template <int NS, int NQ, bool FEW>
 // (the events come as a separate restrict-qualified argument as well, so that the compiler knows no
 // store of the replay reaches them and may read them through the scalar cache)

@@ -1381,7 +1381,7 @@ __device__ __forceinline__ void replay_pool(const rkc_big_args& g, const rkc_poo
     }
   }
   __syncthreads();
-  const u32 status = P.cget(BP::C_STATUS) | (rkc_adds_up(U, P.F, P.A, P.E, P.PR) ? 0u : 0x80000000u);
+  const u32 status = P.cget(BP::C_STATUS) | (rkc_adds_up(U, P.F, P.A, P.E + P.PR) ? 0u : 0x80000000u);
   const u32 queued = P.cget(BP::C_DQL), t2peak = P.cget(BP::C_T2PK);
   i32 v = (i32)P.tv;
   if (l < 10) v += (i32)P.hist[l];

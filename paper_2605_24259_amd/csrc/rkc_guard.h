@@ -20,9 +20,7 @@
 // Blocks left to take after a pass of an eviction loop that took m of K.
 RKC_GUARD_FN uint32_t rkc_left(uint32_t K, uint32_t m) { return K - (m > 1u ? m : 1u); }
 
-// Every usable block is free, active, evictable or protected (cached blocks are evictable or protected).
-RKC_GUARD_FN bool rkc_adds_up(uint32_t U, uint32_t F, uint32_t A, uint32_t E, uint32_t PR) {
-  return F + A + E + PR == U;
-}
+// Every usable block is free (F), active (A) or cached, and every cached block is evictable or protected.
+RKC_GUARD_FN bool rkc_adds_up(uint32_t U, uint32_t F, uint32_t A, uint32_t cached) { return F + A + cached == U; }
 
 #endif

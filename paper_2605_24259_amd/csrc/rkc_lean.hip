@@ -1487,9 +1487,10 @@ __device__ __forceinline__ void replay_pool(const rkc_lean_args& g, const rkc_po
   const u32 nslot_used = P.nslot;
   const u32 vic = P.vic, post = P.post;
   // (the barrier keeps the sum out of the loop of pools that defer or relax, whose registers it would shift:
-  // with it 300 such pools take 480, 545 and 618 us, as without the test, else 488, 554 and 627)
+  // with it 300 such pools take 480, 545 and 618 us, as without the test, else 488, 554 and 627; with four claim
+  // sets it does harm: 2,048 pools of 256 claims 1,727 us with it, 1,682 without)
   u32 cached = P.E + P.PR;
-  if (LP::ext()) asm volatile("" : "+v"(cached));
+  if (LP::ext() && NQ == 1) asm volatile("" : "+v"(cached));
   const u32 status = ufl(P.cold[LP::C_STATUS]) | (rkc_adds_up(U, P.F, P.A, cached) ? 0u : 0x80000000u);
   const u32 queued = ufl(P.cold[LP::C_DQL]);
   const u32 t2peak = ufl(P.cold[LP::C_T2PK]);

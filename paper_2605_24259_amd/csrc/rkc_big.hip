@@ -4,7 +4,7 @@
 // compact kernel's 16-bit encoding that keep to
 //   usable blocks < 2^20, events per pool <= 65,536, shared chains <= 256, live requests <= 16,384,
 //   claim slots <= 65,536 (any number of live claims),
-// where it is the faster one: use_big in rkc_replay.hip weighs the pools that a CU holds at a time, the
+// where it is the faster one: big_pays in rkc_replay.hip weighs the pools that a CU holds at a time, the
 // claim table and the length of the traces.
 // Such batches have few pools per CU (a pool of 262,144 blocks keeps up to 16,384 requests live), so a
 // pool's step is a chain of latencies, and what the general kernel spends it on is memory: its

@@ -1805,19 +1805,20 @@ u64 rounds(const rkc_batch* b, u64 lds, u64 waves) {
 // them are live it wins (the 64 pools of 262,144 blocks 134 and 52 ms); full, they cost 64 pools 79 and
 // 103 ms, 512 pools 159 and 145 ms.  Larger tables lose either way once they fill: 8,000 live claims 70 and
 // 179 ms on 64 pools, 193 and 273 ms on 512.
-// (A batch that would need more scratch there than on the general kernel, where long claim lists may fit in
-// LDS, stays on the general one: the scratch a batch needs never grows.)
-bool use_big(const rkc_batch* b, rkc_big_args* g) {
+bool big_pays(const rkc_batch* b, const rkc_big_args& g, const Layout& L) {
   constexpr i32 kMaxClaims = 4096, kShortTrace = 8;
   constexpr u64 kWavesLds = 16, kWavesScratch = 12, kWavesBig = 24;  // waves a CU's registers hold, by kernel
-  memset(g, 0, sizeof *g);
-  Layout L;
-  if ((b->flags & RKC_FLAG_GENERAL_KERNEL) || b->max_live_claims > kMaxClaims || !rkc_big_layout(b, g) ||
-      !choose_layout(b, &L) || g->scr_pool_bytes > L.scr_pool_bytes)
-    return false;
+  if (b->max_live_claims > kMaxClaims) return false;
   const u64 general = rounds(b, L.lds_bytes, L.global_lists ? kWavesScratch : kWavesLds);
-  const u64 big = rounds(b, g->lds_bytes, kWavesBig);
+  const u64 big = rounds(b, g.lds_bytes, kWavesBig);
   return b->max_events < kShortTrace ? big <= general : 2 * big <= 5 * general;
+}
+
+// The large-pool kernel can take the batch.  (One that would need more scratch there than on the general
+// kernel, where long claim lists may fit in LDS, stays on the general one: the scratch a batch needs never grows.)
+bool big_fits(const rkc_batch* b, rkc_big_args* g, const Layout& L) {
+  memset(g, 0, sizeof *g);
+  return !(b->flags & RKC_FLAG_GENERAL_KERNEL) && rkc_big_layout(b, g) && g->scr_pool_bytes <= L.scr_pool_bytes;
 }
 
 }  // namespace
@@ -1830,11 +1831,22 @@ size_t rkc_scratch_bytes(const rkc_batch* b) {
   if (!b || b->n_pools <= 0) return 0;
   rkc_lean_args lg;
   if (use_lean(b, &lg)) return (size_t)lg.scr_total;
-  rkc_big_args bg;
-  if (use_big(b, &bg)) return (size_t)(bg.scr_pool_bytes * (u64)b->n_pools);
   Layout L;
   if (!choose_layout(b, &L)) return 0;
-  return (size_t)(L.scr_pool_bytes * (u64)b->n_pools);
+  rkc_big_args bg;
+  const bool big = big_fits(b, &bg, L) && big_pays(b, bg, L);
+  return (size_t)((big ? bg.scr_pool_bytes : L.scr_pool_bytes) * (u64)b->n_pools);
+}
+
+// The least scratch that rkc_replay_batch takes: a batch that the general kernel replays faster goes to the
+// large-pool kernel when its scratch is enough there only.
+static u64 least_scratch(const rkc_batch* b) {
+  rkc_lean_args lg;
+  if (use_lean(b, &lg)) return lg.scr_total;
+  Layout L;
+  if (!choose_layout(b, &L)) return 0;
+  rkc_big_args bg;
+  return (big_fits(b, &bg, L) ? bg.scr_pool_bytes : L.scr_pool_bytes) * (u64)b->n_pools;
 }
 
 static rkc_status replay(const rkc_batch* b, void* s) {
@@ -1853,9 +1865,13 @@ static rkc_status replay(const rkc_batch* b, void* s) {
     lg.max_slots = b->max_claim_slots;
     return rkc_tiny_fits(&lg) ? rkc_tiny_launch(&lg, (hipStream_t)s) : rkc_lean_launch(&lg, (hipStream_t)s);
   }
+  Args g;
+  memset(&g, 0, sizeof g);
+  if (!choose_layout(b, &g.L)) return RKC_E_UNSUPPORTED;
+  const u64 need = g.L.scr_pool_bytes * (u64)b->n_pools;
+  if (!b->d_scratch || b->scratch_bytes < least_scratch(b)) return RKC_E_SCRATCH;
   rkc_big_args bg;
-  if (use_big(b, &bg)) {
-    if (!b->d_scratch || b->scratch_bytes < bg.scr_pool_bytes * (u64)b->n_pools) return RKC_E_SCRATCH;
+  if (big_fits(b, &bg, g.L) && (big_pays(b, bg, g.L) || b->scratch_bytes < need)) {
     bg.pools = b->d_pools; bg.events = b->d_events; bg.outcomes = b->d_outcomes;
     bg.pool_tel = b->d_pool_tel; bg.claim_tel = b->d_claim_tel; bg.scratch = b->d_scratch;
     bg.n_events_total = b->n_events_total; bg.n_slots_total = b->n_claim_slots_total;
@@ -1864,11 +1880,6 @@ static rkc_status replay(const rkc_batch* b, void* s) {
     bg.max_slots = b->max_claim_slots;
     return rkc_big_launch(&bg, (hipStream_t)s);
   }
-  Args g;
-  memset(&g, 0, sizeof g);
-  if (!choose_layout(b, &g.L)) return RKC_E_UNSUPPORTED;
-  const u64 need = g.L.scr_pool_bytes * (u64)b->n_pools;
-  if (!b->d_scratch || b->scratch_bytes < need) return RKC_E_SCRATCH;
   g.pools = b->d_pools; g.events = b->d_events; g.outcomes = b->d_outcomes;
   g.pool_tel = b->d_pool_tel; g.claim_tel = b->d_claim_tel; g.scratch = (unsigned char*)b->d_scratch;
   g.n_events_total = b->n_events_total; g.n_slots_total = b->n_claim_slots_total;
@@ -1908,7 +1919,7 @@ rkc_status rkc_replay_batch_noalloc(const rkc_batch* b, void* s) {
   rkc_status st = check_batch(&nb);
   if (st != RKC_OK) return st;
   if (nb.n_pools == 0) return RKC_OK;
-  if (rkc_scratch_bytes(&nb) > (size_t)RKC_NOALLOC_SCRATCH_BYTES) return RKC_E_SCRATCH_LIMIT;
+  if (least_scratch(&nb) > (u64)RKC_NOALLOC_SCRATCH_BYTES) return RKC_E_SCRATCH_LIMIT;
   void* p = noalloc_scratch();
   if (!p) return RKC_E_HIP;
   nb.d_scratch = p;

@@ -230,3 +230,18 @@ def test_relaxation_over_key_groups(oracle_mod, n_chains, n_pools):
     ora = oracle_mod.replay(base.desc, base.events, base.n_claim_slots, threads=16)
     assert ora[1][:, 36].sum() > 100 and ora[1][:, 38].sum() > 50  # relaxed requests, offloaded claims
     compare_tiled(gpu_replay(tile(base, n_pools)), ora)
+
+
+# a batch that is faster on the general kernel, but fits the built-in scratch on the large-pool one only
+def test_builtin_scratch_of_many_large_tables(oracle_mod):
+    import paper_2605_24259_amd as rkc
+    base = randtrace.random_batch(88, 150, U_range=(40, 300), n_events=(20, 64), n_chains=16, tight_every=9, caps=(256, 64),
+                                  defer=True, hard_share=0.5)
+    trace = tile(base, 513)
+    lim = dict(trace.limits(), max_usable_blocks=40000, max_chains=256, max_live_requests=4097, max_live_claims=2500)
+    say("case built-in scratch of many large tables")
+    assert not large_pool_route(trace, lim)
+    db = rkc.DeviceBatch(trace.desc, trace.events, trace.n_claim_slots, lim, scratch=False)
+    assert db.scratch_needed > rkc.NOALLOC_SCRATCH_BYTES
+    ora = oracle_mod.replay(base.desc, base.events, base.n_claim_slots, threads=16)
+    compare_tiled(db.replay_noalloc().results(), ora)
